@@ -317,10 +317,14 @@ int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n);
  * tile variants: V + v is tile v with three stages of operand loads in
  * flight instead of one; the phi phases also take [2V, 2V + 6), kernels
  * that keep the phi basis in LDS and stream the data straight into MFMA
- * fragments (unfolded), and [2V + 6, 2V + 14), the same kernels folded
- * about the patch's central meridian (h = ceil(n_phi / 2) cells per row;
- * YYG_ERR_UNSUPPORTED on a grid whose rows are not mirror-symmetric, the
- * condition under which the tile variants of the phi phases fold too); the
+ * fragments (unfolded), and [2V + 6, 2V + 14), kernels folded about the
+ * patch's central meridian and, on a grid that is symmetric about them
+ * (every one whose cell spacing divides 180 degrees), the meridians 90
+ * degrees off it (YYG_ERR_UNSUPPORTED on a grid whose rows are not
+ * mirror-symmetric, the condition under which the tile variants of the phi
+ * phases fold too); a plan starts from one of these.  The first three hold
+ * their basis in registers and walk row tiles, the others sweep one row
+ * tile per wave; the
  * phi synthesis also [2V + 14, 2V + 18), folded kernels in which every wave
  * loads its matrix-core operands straight from memory (no LDS; the same
  * mirror-symmetry condition).  Every phase then takes 12 further variants

@@ -165,7 +165,7 @@ struct yyg_grid {
     // variants use these when the grid is mirror-symmetric: fold = true)
     bool fold = false;
     long h = 0, ldkh = 0, ks = 0, ldtf = 0;  // folded length, its row stride; synthesis split and row stride
-    long kca = 0, nba = 0, kcs = 0, nks = 0;  // folded LDS-basis kernels: cos rows / slots and totals
+    long kcs = 0, nks = 0;   // LDS-free synthesis: cos slots and all slots
     double *WF = nullptr;    // folded analysis basis [n_t][2][L+1][ldkh]: even (cos) / odd (sin) halves
     double *TF = nullptr;    // folded synthesis basis [h][ldtf]: cos m at m, sin m at ks + m - 1
     yyg::GemmF64Args phi_ana_f{}, phi_syn_f{};
@@ -177,11 +177,10 @@ struct yyg_grid {
     // (m <= L), sin m at slot ks + m - 1, [n_t][ks + L][ldkh], exact weights
     double *WFAB = nullptr;
     yyg::GemmF64Args phi_ana_ab{};
-    // folded LDS-basis kernels: the cos / sin halves without padding each to
-    // the tile width
-    double *WFD = nullptr;   // analysis basis [n_t][kca + 16 ceil(L/16)][h]: cos m at row m, sin m at kca + m - 1
-    double *TFD = nullptr;   // synthesis basis [h][kcs + 4 ceil(L/4)]: cos m at slot m, sin m at kcs + m - 1
-    yyg::PhiDirectArgs phi_ana_fd{}, phi_syn_fd{};
+    // folded about the central meridian and, where the grid allows, the
+    // meridians 90 degrees off it
+    yyg::PhiQuadArgs quad_ana{}, quad_syn{};
+    double *QA = nullptr, *QS = nullptr, *QW = nullptr;  // their bases and the analysis weights
     // folded phi synthesis with the fragments loaded straight from memory
     double *BK = nullptr;    // its basis, slot-major [kcs + 4 ceil(L/4)][hp]
     long hp = 0;             // h padded to a multiple of 32
@@ -191,11 +190,11 @@ struct yyg_grid {
     // variant per phase (0 phi analysis, 1 theta analysis, 2 moment
     // rotation, 3 theta synthesis, 4 phi synthesis): v < V the tile v,
     // V + v the same with the deep prefetch, 2V + d (phi phases) the
-    // LDS-basis kernel d, 2V + D + f (phi phases, fold) the folded
-    // LDS-basis kernel f, 2V + D + F + e (phi synthesis, fold) the LDS-free
+    // LDS-basis kernel d, 2V + D + f (phi phases, fold) the kernel f folded
+    // about two meridians, 2V + D + F + e (phi synthesis, fold) the LDS-free
     // kernel e
     // defaults (before autotuning): 32 x 32 tiles, 64 x 32 for the theta
-    // synthesis
+    // synthesis; the phi phases of a folded grid as sep_default_phi
     int var[5] = {10, 10, 10, 9, 10};
     // reduced-precision phi transforms (FP32, BF16 x 3): tile of the phi
     // analysis and of the phi synthesis (yyg::sep_lp_tile_count() shapes)
@@ -216,7 +215,7 @@ hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 void sep_release(yyg_grid *g) {
   auto &S = g->sep;
   double **b[] = {&S.Wcs, &S.trig, &S.T2, &S.P2, &S.Drot, &S.X2, &S.V,   &S.Ut,  &S.coefS,
-                  &S.At,  &S.WF,   &S.TF, &S.WFD, &S.TFD,  &S.BK, &S.WFAB, &S.CSF, &S.Wt};
+                  &S.At,  &S.WF,   &S.TF, &S.QA, &S.QS, &S.QW, &S.BK, &S.WFAB, &S.CSF, &S.Wt};
   for (double **x : b) {
     if (*x) (void)dev_free(*x);
     *x = nullptr;
@@ -360,13 +359,14 @@ namespace {
 // Variants of separable phase r: v < V the tile v, V + v the same with
 // three stages of loads in flight (V = the FP64 tile variants); the phi
 // phases (0, 4) also 2V + d, the LDS-basis kernel variant d (d < D), and
-// 2V + D + f, its folded form f (F of them; mirror-symmetric grids only);
+// 2V + D + f, the kernel f folded about two meridians (F of them;
+// mirror-symmetric grids only);
 // the phi synthesis also 2V + D + F + e, the LDS-free folded kernel e.
 // Every phase then takes X = yyg::x4_variant_count() tiles on the 4x4x4
 // FP64 MFMA at the end of its range (sep_x4_base).
 int sep_x4_base(int r) {
   const int v = 2 * yyg::gemm_f64_variant_count();
-  const int phi = yyg::phi_direct_variant_count() + yyg::phi_fold_variant_count();
+  const int phi = yyg::phi_direct_variant_count() + yyg::phi_quad_variant_count();
   return r == 0 ? v + phi : r == 4 ? v + phi + yyg::phi_lean_variant_count() : v;
 }
 
@@ -412,7 +412,7 @@ int sep_set_variant(yyg_grid *g, int r, int v) {
 hipError_t sep_launch_phase(yyg_grid *g, int r, hipStream_t s) {
   auto &S = g->sep;
   const int nv = yyg::gemm_f64_variant_count(), nd = yyg::phi_direct_variant_count();
-  const int nf = yyg::phi_fold_variant_count();
+  const int nf = yyg::phi_quad_variant_count();
   if (r == 4 && S.var[r] >= sep_stream_base(4))
     return yyg::launch_phi_syn_stream(S.var[r] - sep_stream_base(4), S.phi_syn_s, g->cus, s);
   if (r == 0 && S.var[r] >= sep_xcol_base(0)) return yyg::launch_fold_xcol(S.var[r] - sep_xcol_base(0), S.phi_ana_f, s);
@@ -424,8 +424,9 @@ hipError_t sep_launch_phase(yyg_grid *g, int r, hipStream_t s) {
     return yyg::launch_x4_sep_phase(S.var[r] - sep_x4_base(r), r, S.fold, phi, S.phi_ana_ab, S.args, s);
   }
   if (r == 4 && S.var[r] >= 2 * nv + nd + nf) return yyg::launch_phi_syn_lean(S.var[r] - 2 * nv - nd - nf, S.phi_syn_l, s);
-  if (sep_fold_variant(r, S.var[r]))
-    return yyg::launch_phi_fold(S.var[r] - 2 * nv - nd, r == 0, r == 0 ? S.phi_ana_fd : S.phi_syn_fd, s);
+  if (sep_fold_variant(r, S.var[r])) {
+    return yyg::launch_phi_quad(S.var[r] - 2 * nv - nd, r == 0, r == 0 ? S.quad_ana : S.quad_syn, g->cus, s);
+  }
   if ((r == 0 || r == 4) && S.var[r] >= 2 * nv)
     return yyg::launch_phi_direct(S.var[r] - 2 * nv, r == 0, r == 0 ? S.phi_ana_d : S.phi_syn_d, s);
   const int v = S.var[r] % nv;
@@ -454,11 +455,11 @@ void sep_bind_work(yyg_grid *g, const SepWork &w) {
   S.At = w.At;
   g->d_Ahat = w.Ahat;
   S.phi_ana.C = S.phi_ana_f.C = S.phi_ana_ab.C = w.X2;
-  S.phi_ana_d.C = S.phi_ana_fd.C = w.X2;
+  S.phi_ana_d.C = S.quad_ana.C = w.X2;
   S.phi_syn.A = S.phi_syn_f.A = w.V;
   S.phi_syn_s.V = w.V;
   S.phi_ana_s.X2 = w.X2;
-  S.phi_syn_d.X = S.phi_syn_fd.X = w.V;
+  S.phi_syn_d.X = S.quad_syn.X = w.V;
   S.phi_syn_l.V = w.V;
   S.args.X2 = w.X2;
   S.args.Ut = w.Ut;
@@ -488,10 +489,106 @@ int sep_set_pointers(yyg_grid *g, const double *rho, double *phi, hipStream_t) {
   g->sep.phi_ana_ab.A = rho;
   g->sep.phi_syn_f.C = phi;
   g->sep.phi_syn_s.phi = phi;
-  g->sep.phi_ana_fd.X = rho;
-  g->sep.phi_syn_fd.C = phi;
+  g->sep.quad_ana.X = rho;
+  g->sep.quad_syn.C = phi;
   g->sep.phi_syn_l.C = phi;
   return YYG_OK;
+}
+
+// The fold about two meridians (yyg::PhiQuadArgs): its index ranges, bases
+// and weights.  The central fold holds (S.fold); the one about the meridians
+// 90 degrees off the centre pairs front cells k and cc - k where the cell
+// spacing divides 180 degrees (cc = np - 1 - 180 / spacing) and the C / S and
+// trig tables show the parity to 1e-12 of their largest entry.  The tables
+// halve a cell that is its own mirror or partner.
+void sep_quad_tables(yyg_grid *g, const std::vector<double> &CSt, const std::vector<double> &trig,
+                     std::vector<double> &QA, std::vector<double> &QS, std::vector<double> &QW) {
+  auto &S = g->sep;
+  const int L = g->L, nt = g->n_t, np = g->n_p, h = (int)S.h;
+  auto mcol = [](int gr, int o, int *m) {
+    *m = 2 * o + (gr == 0 ? 0 : gr == 2 ? 2 : 1);
+    return gr < 2 ? std::max(2 * *m - 1, 0) : 2 * *m;
+  };
+  const double spacing = g->geom.ph[1] - g->geom.ph[0], ccx = np - 1 - M_PI / spacing;
+  int cc = (int)std::lround(ccx);
+  bool pair = std::fabs(ccx - cc) < 1e-6 && cc >= 1 && cc < h;
+  if (pair) {
+    double cmax = 0.0, bad = 0.0, tbad = 0.0;
+    for (double v : CSt) cmax = std::max(cmax, std::fabs(v));
+    for (int k = 0; k <= cc; ++k)
+      for (int mc = 0; mc < 2 * L + 1; ++mc) {
+        const int m = (mc + 1) / 2;
+        const double sg = (m % 2 ? -1.0 : 1.0) * ((mc > 0 && mc % 2 == 0) ? -1.0 : 1.0);
+        bad = std::max(bad, std::fabs(CSt[(size_t)mc * S.ldk + k] - sg * CSt[(size_t)mc * S.ldk + cc - k]));
+        tbad = std::max(tbad, std::fabs(trig[(size_t)k * S.ldm + mc] - sg * trig[(size_t)(cc - k) * S.ldm + mc]));
+      }
+    pair = bad <= 1e-12 * cmax && tbad <= 1e-12;
+  }
+  const int f0 = pair ? (cc + 1) / 2 : 0, T2 = pair ? cc - f0 + 1 : 0, K = h - f0;
+  // the analysis loads pairs of points: its partners end on a whole pair
+  const int pad = T2 % 2;
+  auto &A = S.quad_ana, &B = S.quad_syn;
+  A.f0 = f0 - pad;
+  A.tlo = pad;
+  A.K = K + pad;
+  A.T2 = pair ? T2 + pad : 0;
+  B.f0 = f0;
+  B.tlo = 0;
+  B.K = K;
+  B.T2 = T2;
+  A.cc = B.cc = pair ? cc : 0;
+  A.S = (A.K + 15) / 16;
+  B.S = (K + 15) / 16;
+  A.Kp = 16 * A.S;
+  B.Kp = 16 * B.S;
+  const int tj = yyg::phi_quad_tiles(L), ch = yyg::phi_quad_chunk(L);
+  QA.assign((size_t)A.S * ch, 0.0);
+  auto half = [&](int f) { return (np - 1 - f == f ? 0.5 : 1.0) * (pair && cc - f == f ? 0.5 : 1.0); };
+  for (int t = A.tlo; t < A.K; ++t) {
+    const int f = A.f0 + t, s = t / 16, g4 = t % 16 / 4, hf = t % 4 / 2;
+    double *c = &QA[(size_t)s * ch];
+    for (int gr = 0; gr < 4; ++gr)
+      for (int o = 0, m; o < 16 * tj; ++o) {
+        const int mc = mcol(gr, o, &m);
+        if (m <= L)
+          c[((gr * tj + o / 16) * 2 + hf) * 128 + 2 * (16 * g4 + o % 16) + t % 2] = half(f) * CSt[(size_t)mc * S.ldk + f];
+      }
+    if (yyg::phi_quad_extra(L)) c[4 * tj * 256 + t % 16] = half(f) * CSt[(size_t)(2 * L - 1) * S.ldk + f];
+  }
+  const int nq2 = (yyg::phi_quad_steps(L) + 1) / 2;
+  QS.assign((size_t)((B.S + 1) / 2 * 2) * 4 * nq2 * 128, 0.0);
+  for (int t = 0; t < K; ++t) {
+    double *c = &QS[(size_t)(t / 16) * 4 * nq2 * 128];
+    for (int gr = 0; gr < 4; ++gr)
+      for (int o = 0, m; o < 8 * nq2; ++o) {
+        const int mc = mcol(gr, o, &m), q = o / 4;
+        if (m <= L) c[(gr * nq2 + q / 2) * 128 + 2 * (16 * (o % 4) + t % 16) + q % 2] = trig[(size_t)(f0 + t) * S.ldm + mc];
+      }
+  }
+  QW.clear();
+  if (g->n_patch == 2) {
+    QW.assign((size_t)nt * 2 * A.Kp, 0.0);
+    auto wmean = [&](int j, int k) {
+      return 0.5 * (g->w_host[(size_t)j * np + k] + g->w_host[(size_t)j * np + np - 1 - k]);
+    };
+    for (int j = 0; j < nt; ++j)
+      for (int t = A.tlo; t < A.K; ++t) {
+        QW[((size_t)j * 2 + 0) * A.Kp + t] = wmean(j, A.f0 + t);
+        if (t < A.T2) QW[((size_t)j * 2 + 1) * A.Kp + t] = wmean(j, cc - A.f0 - t);
+      }
+  }
+}
+
+// Default kernels of the phi phases on a folded grid.
+void sep_default_phi(yyg_grid *g) {
+  auto &S = g->sep;
+  const int base = 2 * yyg::gemm_f64_variant_count() + yyg::phi_direct_variant_count();
+  const int ana = yyg::phi_quad_default(true, S.quad_ana, g->cus);
+  // without partners a short analysis gains nothing from the parity split:
+  // 131 shells of 61 x 187 cells, lmax 23: 11.2 us in the 32 x 32 tiles, 11.6
+  // in the sweep
+  if (ana == 0 || S.quad_ana.T2 > 0) S.var[0] = base + ana;
+  S.var[4] = base + yyg::phi_quad_default(false, S.quad_syn, g->cus);
 }
 
 int sep_build(yyg_grid *g) {
@@ -503,7 +600,7 @@ int sep_build(yyg_grid *g) {
   S.ldm = round_up(nmc, 16);
   S.ldl = round_up(L + 1, 16);
   if (!yyg::radial_scan_q_supports(g->n_r, g->n_patch)) return YYG_ERR_UNSUPPORTED;
-  std::vector<double> CSt, Wcs, trig, T, P, T2, P2, D, coef, coefS, WF, TF, WFD, TFD, BK, WFAB, CSF, WTF;
+  std::vector<double> CSt, Wcs, trig, T, P, T2, P2, D, coef, coefS, WF, TF, BK, WFAB, CSF, WTF, QA, QS, QW;
   int nte = 0, nto = 0, ldcs = 0;
   try {
     coef.resize((size_t)4 * g->n_r * (L + 1));
@@ -604,32 +701,18 @@ int sep_build(yyg_grid *g) {
             WFAB[(base + m) * S.ldkh + k] = WF[(((size_t)j * 2 + 0) * (L + 1) + m) * S.ldkh + k];
             if (m > 0) WFAB[(base + S.ks + m - 1) * S.ldkh + k] = WF[(((size_t)j * 2 + 1) * (L + 1) + m - 1) * S.ldkh + k];
           }
-      // the same for the folded LDS-basis kernels: the cos half padded to a
-      // multiple of 16 rows (analysis) / 4 slots (synthesis), the sin half
-      // after it
-      S.kca = round_up(L + 1, 16);
+      // the synthesis basis slot-major for the LDS-free kernel: cos m at slot
+      // m, sin m at kcs + m - 1, cells padded to a multiple of 32
       S.kcs = round_up(L + 1, 4);
-      S.nba = S.kca + round_up(L, 16);
       S.nks = S.kcs + round_up(L, 4);
-      WFD.assign((size_t)nt * S.nba * h, 0.0);
-      TFD.assign((size_t)h * S.nks, 0.0);
-      for (int j = 0; j < nt; ++j)
-        for (int m = 0; m <= L; ++m)
-          for (int k = 0; k < h; ++k) {
-            const double *wf = &WF[((size_t)j * 2 * (L + 1)) * S.ldkh + k];
-            WFD[((size_t)j * S.nba + m) * h + k] = wf[(size_t)m * S.ldkh];
-            if (m > 0) WFD[((size_t)j * S.nba + S.kca + m - 1) * h + k] = wf[(size_t)(L + 1 + m - 1) * S.ldkh];
-          }
-      for (int k = 0; k < h; ++k)
-        for (int m = 0; m <= L; ++m) {
-          TFD[(size_t)k * S.nks + m] = TF[(size_t)k * S.ldtf + m];
-          if (m > 0) TFD[(size_t)k * S.nks + S.kcs + m - 1] = TF[(size_t)k * S.ldtf + S.ks + m - 1];
-        }
-      // the same synthesis basis slot-major, cells padded to a multiple of 32
       S.hp = round_up(h, 32);
       BK.assign((size_t)S.nks * S.hp, 0.0);
-      for (long sl = 0; sl < S.nks; ++sl)
-        for (int k = 0; k < h; ++k) BK[(size_t)sl * S.hp + k] = TFD[(size_t)k * S.nks + sl];
+      for (int k = 0; k < h; ++k)
+        for (int m = 0; m <= L; ++m) {
+          BK[(size_t)m * S.hp + k] = TF[(size_t)k * S.ldtf + m];
+          if (m > 0) BK[(size_t)(S.kcs + m - 1) * S.hp + k] = TF[(size_t)k * S.ldtf + S.ks + m - 1];
+        }
+      sep_quad_tables(g, CSt, trig, QA, QS, QW);
     }
     T.resize((size_t)nt * Q);
     yyg::theta_table_normalised(g->geom, L, T.data());
@@ -666,8 +749,9 @@ int sep_build(yyg_grid *g) {
   if (st == YYG_OK) st = dmalloc(&S.coefS, coefS.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.WF, WF.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.TF, TF.size());
-  if (st == YYG_OK && S.fold) st = dmalloc(&S.WFD, WFD.size());
-  if (st == YYG_OK && S.fold) st = dmalloc(&S.TFD, TFD.size());
+  if (st == YYG_OK && S.fold) st = dmalloc(&S.QA, QA.size());
+  if (st == YYG_OK && S.fold) st = dmalloc(&S.QS, QS.size());
+  if (st == YYG_OK && !QW.empty()) st = dmalloc(&S.QW, QW.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.BK, BK.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.WFAB, WFAB.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.CSF, CSF.size());
@@ -689,8 +773,9 @@ int sep_build(yyg_grid *g) {
   if (S.fold) {
     chk(hipMemcpy(S.WF, WF.data(), WF.size() * sizeof(double), hipMemcpyHostToDevice));
     chk(hipMemcpy(S.TF, TF.data(), TF.size() * sizeof(double), hipMemcpyHostToDevice));
-    chk(hipMemcpy(S.WFD, WFD.data(), WFD.size() * sizeof(double), hipMemcpyHostToDevice));
-    chk(hipMemcpy(S.TFD, TFD.data(), TFD.size() * sizeof(double), hipMemcpyHostToDevice));
+    chk(hipMemcpy(S.QA, QA.data(), QA.size() * sizeof(double), hipMemcpyHostToDevice));
+    chk(hipMemcpy(S.QS, QS.data(), QS.size() * sizeof(double), hipMemcpyHostToDevice));
+    if (S.QW) chk(hipMemcpy(S.QW, QW.data(), QW.size() * sizeof(double), hipMemcpyHostToDevice));
     chk(hipMemcpy(S.BK, BK.data(), BK.size() * sizeof(double), hipMemcpyHostToDevice));
     chk(hipMemcpy(S.WFAB, WFAB.data(), WFAB.size() * sizeof(double), hipMemcpyHostToDevice));
     chk(hipMemcpy(S.CSF, CSF.data(), CSF.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -740,10 +825,22 @@ int sep_build(yyg_grid *g) {
                                       nmc, ldcs, nte, nto};
   S.phi_ana_d = yyg::PhiDirectArgs{nullptr, S.Wcs, S.X2, (int)M, nt, nmc, np, S.ldk, (long)nmc * S.ldk};
   S.phi_syn_d = yyg::PhiDirectArgs{S.V, S.trig, nullptr, (int)M, nt, np, nmc, S.ldm, 0};
-  S.phi_ana_fd = yyg::PhiDirectArgs{nullptr, S.WFD, S.X2, (int)M, nt, (int)S.nba, (int)S.h, S.h, S.nba * S.h,
-                                    np, (int)S.kca, nmc};
-  S.phi_syn_fd = yyg::PhiDirectArgs{S.V, S.TFD, nullptr, (int)M, nt, (int)S.h, (int)S.nks, S.nks, 0,
-                                    np, (int)S.kcs, nmc};
+  if (S.fold) {
+    for (yyg::PhiQuadArgs *q : {&S.quad_ana, &S.quad_syn}) {
+      q->MJ = MJ;
+      q->ld = (long)nt * np;
+      q->Mr = (int)M;
+      q->nt = nt;
+      q->np = np;
+      q->L = L;
+    }
+    S.quad_ana.bas = S.QA;
+    S.quad_ana.W = S.QW;
+    S.quad_ana.C = S.X2;
+    S.quad_syn.bas = S.QS;
+    S.quad_syn.X = S.V;
+    sep_default_phi(g);
+  }
   S.phi_syn_l = yyg::PhiLeanArgs{S.V, S.BK, nullptr, (int)M, nt, np, (int)S.h, (int)S.hp, (int)S.nks, (int)S.kcs, nmc};
   // theta analysis, rotation (Yin-Yang) and theta synthesis: problem
   // operands derived in the kernels from these
@@ -1549,7 +1646,7 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
       g->sep.phi_syn_d.C = nullptr;
       g->sep.phi_syn_f.C = nullptr;
       g->sep.phi_syn_s.phi = nullptr;
-      g->sep.phi_syn_fd.C = nullptr;
+      g->sep.quad_syn.C = nullptr;
       g->sep.phi_syn_l.C = nullptr;
     }
     if (e != hipSuccess) {
@@ -1992,8 +2089,8 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
     g->sep.phi_ana_ab.A = nullptr;
     g->sep.phi_syn_f.C = nullptr;
     g->sep.phi_syn_s.phi = nullptr;
-    g->sep.phi_ana_fd.X = nullptr;
-    g->sep.phi_syn_fd.C = nullptr;
+    g->sep.quad_ana.X = nullptr;
+    g->sep.quad_syn.C = nullptr;
     g->sep.phi_syn_l.C = nullptr;
     if (st3 != YYG_OK) return st3;
   }
@@ -2109,12 +2206,18 @@ int yyg_sep_kernel(const yyg_grid *g, int phase, char *name, size_t n) {
     return YYG_OK;
   }
   const int v = g->sep.var[phase], x0 = sep_x4_base(phase);
+  const int quad = 2 * yyg::gemm_f64_variant_count() + yyg::phi_direct_variant_count();
+  const int lean = quad + yyg::phi_quad_variant_count();
   const int r = phase == 4 && v >= sep_stream_base(4) ? yyg::phi_stream_kernel_name(v - sep_stream_base(4), name, n)
                 : phase == 0 && v >= sep_xcol_base(0) ? yyg::fold_xcol_kernel_name(v - sep_xcol_base(0), name, n)
                 : phase == 0 && v >= sep_stream_base(0)
                     ? yyg::phi_ana_stream_kernel_name(v - sep_stream_base(0), name, n)
-                : v >= x0 ? yyg::x4_kernel_name(v - x0, phase, g->sep.fold, name, n)
-                          : yyg::sep_kernel_name(phase, v, g->sep.fold, name, n);
+                : v >= x0                    ? yyg::x4_kernel_name(v - x0, phase, g->sep.fold, name, n)
+                : phase == 4 && v >= lean    ? yyg::phi_lean_kernel_name(v - lean, name, n)
+                : !sep_fold_variant(phase, v) ? yyg::sep_kernel_name(phase, v, g->sep.fold, name, n)
+                                             : yyg::phi_quad_kernel_name(v - quad, phase == 0,
+                                                                         phase == 0 ? g->sep.quad_ana : g->sep.quad_syn,
+                                                                         name, n);
   return r == 0 ? YYG_OK : YYG_ERR_INVALID_ARG;
 }
 

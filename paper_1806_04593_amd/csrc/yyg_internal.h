@@ -118,24 +118,47 @@ struct SepPhaseArgs {
 //             N ldb);
 //  synthesis: C = phi[row][j][k] (N = n_p) from X = V [mc][j][row] (K = 2L+1)
 //             and bas = trig [k][ldb] (bas_batch = 0).
-// The folded forms (launch_phi_fold) run over h = ceil(n_p / 2) cells:
-//  analysis:  N = the folded basis rows (cos m at row m, sin m at row kc +
-//             m - 1; kc a multiple of 16), K = h, bas = [j][N][ldb];
-//  synthesis: N = h, K = the contraction slots (cos m at slot m, sin m at
-//             slot kc + m - 1; kc a multiple of 4), bas = [h][ldb]
-//             (bas_batch = 0);
-// with np = n_p and nmc = 2L+1 the azimuthal columns.
 struct PhiDirectArgs {
   const double *X, *bas;
   double *C;
   int M, nt, N, K;  // rows, colatitudes, basis rows, contraction length
   long ldb, bas_batch;
-  int np = 0, kc = 0, nmc = 0;  // folded forms only
 };
 int phi_direct_variant_count();
 hipError_t launch_phi_direct(int variant, bool analysis, const PhiDirectArgs &a, hipStream_t s);
-int phi_fold_variant_count();
-hipError_t launch_phi_fold(int variant, bool analysis, const PhiDirectArgs &a, hipStream_t s);
+
+// Phi transforms folded about the central meridian and, where the grid has
+// them, the meridians 90 degrees off it (yyg_phi_quad.hip).  Fold index t
+// stands for the front cell f = f0 + t, its mirror np - 1 - f and, for t <
+// T2, the partners cc - f and np - 1 - cc + f.
+//  analysis:  X = rho [row][j][np], C = X2 [mc][j][row]; bas holds S stages
+//             of 16 points of phi_quad_chunk(L) doubles, in operand order
+//             [group][tile][half][lane][2]: lane (g, o) of a wave has
+//             output 16 tile + o at points 4 g + 2 half + {0, 1}, then (if
+//             phi_quad_extra(L)) the last even cosine's 16 points.  Points
+//             below tlo or from K on are padding (basis zero); T2 is
+//             even.  W = overlap weights [j][front / partner][Kp]
+//             (a mirror pair's mean), null when all are 1.
+//  synthesis: X = V [mc][j][row], C = phi [row][j][np]; bas holds S tiles of
+//             16 cells (rounded up to a whole pair), [group][ceil(steps / 2)][lane][2]: lane (g, c) has
+//             cell c at columns 4 q + g of the group, q = 2 pair + {0, 1}.
+// Groups: cosines of even m (m = 2 o), of odd m (2 o + 1), sines of even m
+// (2 o + 2), of odd m (2 o + 1).
+struct PhiQuadArgs {
+  const double *X, *bas, *W;
+  double *C;
+  long MJ, ld;  // nt * Mr; nt * np
+  int Mr, nt, np, L;
+  int f0, cc, tlo, K, T2, S, Kp;
+};
+int phi_quad_tiles(int L);   // 16-wide output tiles per group
+bool phi_quad_extra(int L);  // one more even cosine than those hold
+int phi_quad_chunk(int L);   // doubles of an analysis basis stage
+int phi_quad_steps(int L);   // synthesis steps of four columns per group
+int phi_quad_variant_count();
+int phi_quad_default(bool analysis, const PhiQuadArgs &a, int cus);  // the variant of a plan not tuned
+hipError_t launch_phi_quad(int v, bool analysis, const PhiQuadArgs &a, int cus, hipStream_t s);
+int phi_quad_kernel_name(int v, bool analysis, const PhiQuadArgs &a, char *buf, size_t n);
 
 // Folded phi synthesis with every wave loading its MFMA fragments straight
 // from memory (no LDS): phi[row][j][k] for k < h = ceil(n_p / 2) and the
@@ -150,6 +173,7 @@ struct PhiLeanArgs {
 };
 int phi_lean_variant_count();
 hipError_t launch_phi_syn_lean(int variant, const PhiLeanArgs &a, hipStream_t s);
+int phi_lean_kernel_name(int v, char *buf, size_t n);
 
 // FP64 tiles on v_mfma_f64_4x4x4f64 (kGemmX4) for the separable phases:
 // x4_variant_count() shapes; phase 0 / 4 are the phi transforms (folded

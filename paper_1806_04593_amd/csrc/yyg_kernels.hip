@@ -319,24 +319,9 @@ __global__ void expand_self_basis_kernel(const double *__restrict__ P, const dou
 //            MFMA's A side is the basis (rows mc), the B side the data.
 //  synthesis:       phi[row][j][k] = sum_mc V[mc][j][row] trig[k][mc]; the
 //            A side is the data (rows), the B side the basis (rows k).
-// FOLD: every row of n_p cells is even (cos) / odd (sin) about its middle,
-// so the transforms run over h = ceil(n_p / 2) cells (the kGemmFoldA /
-// kGemmFoldC forms, without their padding of each half to 16):
-//  analysis:  basis rows kc (a multiple of 16) apart: row i < kc is cos m =
-//             i, row i >= kc sin m = i - kc + 1 (W_j folded, K = h); a cos
-//             tile multiplies rho[k] + rho[n_p - 1 - k], a sin tile
-//             rho[k] - rho[n_p - 1 - k]; row i lands at azimuthal column mc
-//             (dropped when mc >= nmc);
-//  synthesis: contraction slots in steps of 4 consecutive slots, slot s < kc
-//             (a multiple of 4) cos m = s, beyond sin m = s - kc + 1; the data
-//             of a slot is V's azimuthal column mc (clamped below nmc; the
-//             basis is zero at padding slots); the cos steps sum the even
-//             part e, the sin steps the odd part o, and cell k < h gets
-//             e + o, its mirror n_p - 1 - k gets e - o.
-template <bool ANA, int WAVES, int NT, int NBUF, bool FOLD>
+template <bool ANA, int WAVES, int NT, int NBUF>
 __global__ __launch_bounds__(64 * WAVES) void phi_direct_kernel(PhiDirectArgs a) {
   constexpr int G = 16 * NT, KC = 64, NTH = 64 * WAVES, PF = 4;
-  constexpr bool FA = FOLD && ANA, FS = FOLD && !ANA;
   constexpr int EL = (G * KC + NTH - 1) / NTH;  // basis chunk elements per thread
   __shared__ __align__(16) double sB[NBUF][G][KC + 2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -344,7 +329,7 @@ __global__ __launch_bounds__(64 * WAVES) void phi_direct_kernel(PhiDirectArgs a)
   const int j = blockIdx.y, g0 = blockIdx.z * G;
   const int r0 = blockIdx.x * (16 * WAVES) + 16 * wave;
   const int M = a.M, N = a.N, K = a.K, nt = a.nt;
-  const int np = FOLD ? a.np : (ANA ? K : N);  // cells per row
+  const int np = ANA ? K : N;  // cells per row
   const double *__restrict__ bas = a.bas + (long)j * a.bas_batch;
   // this lane's data row (clamped) and its view of the contraction index
   const int row = min(r0 + lr, M - 1);
@@ -352,115 +337,68 @@ __global__ __launch_bounds__(64 * WAVES) void phi_direct_kernel(PhiDirectArgs a)
       ANA ? a.X + (long)row * ((long)nt * np) + (long)j * np : a.X + (long)j * M + row;
   const long xk = ANA ? 1 : (long)nt * M;  // stride of the contraction index
   // contraction slot of step s of stage st: each lane four consecutive
-  // slots (one per step) or, FS, each step four consecutive slots
-  auto slot = [&](int st, int s) { return FS ? 16 * st + 4 * s + lg : 16 * st + 4 * lg + s; };
-  double xs[PF][4], xm[FA ? PF : 1][4];
+  // slots (one per step)
+  auto slot = [&](int st, int s) { return 16 * st + 4 * lg + s; };
+  double xs[PF][4];
   double stg[EL];
-  // FS: acc sums the cos slots (even part), acc2 the sin slots (odd part)
-  dbl4 acc[NT], acc2[FS ? NT : 1];
+  dbl4 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
-  if constexpr (FS) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc2[FS ? t : 0] = dbl4{0.0, 0.0, 0.0, 0.0};
-  }
 
-  // The contraction over slots [kb, kb + kn) into ac: data fragments PF
-  // stages ahead in registers, the basis in chunks of KC slots through LDS.
-  auto run = [&](dbl4 (&ac)[NT], int kb, int kn) {
-    auto xload = [&](int st, int q) {
+  // The contraction: data fragments PF stages ahead in registers, the basis
+  // in chunks of KC slots through LDS.
+  auto xload = [&](int st, int q) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = kb + min(slot(st, s), kn - 1);
-        if constexpr (FS) {
-          const int m = k < a.kc ? k : k - a.kc + 1;
-          const int mc = min(k < a.kc ? max(2 * m - 1, 0) : 2 * m, a.nmc - 1);
-          xs[q][s] = xr[(long)mc * xk];
-        } else {
-          xs[q][s] = xr[(long)k * xk];
-          if constexpr (FA) xm[FA ? q : 0][s] = xr[np - 1 - k];
-        }
-      }
-    };
-    auto bload = [&](int c) {
+    for (int s = 0; s < 4; ++s) xs[q][s] = xr[(long)min(slot(st, s), K - 1) * xk];
+  };
+  auto bload = [&](int c) {
 #pragma unroll
-      for (int u = 0; u < EL; ++u) {
-        const int e = min(tid + NTH * u, G * KC - 1), br = e / KC, kk = e % KC;
-        stg[u] = bas[(long)min(g0 + br, N - 1) * a.ldb + kb + min(c * KC + kk, kn - 1)];
-      }
-    };
-    auto bstore = [&](int c, int buf) {
-#pragma unroll
-      for (int u = 0; u < EL; ++u) {
-        const int e = tid + NTH * u, br = e / KC, kk = e % KC;
-        if (e < G * KC) sB[buf][br][kk] = keep_if(g0 + br < N && c * KC + kk < kn, stg[u]);
-      }
-    };
-    const int nst = (kn + 15) / 16, nch = (kn + KC - 1) / KC;
-#pragma unroll
-    for (int p = 0; p < PF; ++p) xload(min(p, nst - 1), p);
-    bload(0);
-    __builtin_amdgcn_sched_barrier(0);
-    bstore(0, 0);
-    __syncthreads();
-    for (int c = 0; c < nch; ++c) {
-      const int buf = NBUF == 2 ? (c & 1) : 0;
-      if (c + 1 < nch) bload(c + 1);
-      // the chunk's four stages; stage st = 4c + q sits in register slot q
-#pragma unroll
-      for (int q = 0; q < KC / 16; ++q) {
-        const int st = c * (KC / 16) + q;
-        if (st < nst) {  // uniform
-          double bf[NT][4];
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) bf[t][s] = sB[buf][16 * t + lr][slot(q, s)];
-          if constexpr (FA) {
-            // the even and odd parts of the data; a tile is all cos or all sin
-            double de[4], dd[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              de[s] = xs[q][s] + xm[FA ? q : 0][s];
-              dd[s] = xs[q][s] - xm[FA ? q : 0][s];
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-              for (int t = 0; t < NT; ++t)
-                ac[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[t][s], g0 + 16 * t < a.kc ? de[s] : dd[s], ac[t], 0,
-                                                             0, 0);
-          } else if constexpr (FS) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-              if (16 * st + 4 * s < kn) {  // uniform: steps past the end skipped
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                  ac[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(xs[q][s], bf[t][s], ac[t], 0, 0, 0);
-              }
-          } else {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-              for (int t = 0; t < NT; ++t)
-                ac[t] = ANA ? __builtin_amdgcn_mfma_f64_16x16x4f64(bf[t][s], xs[q][s], ac[t], 0, 0, 0)
-                            : __builtin_amdgcn_mfma_f64_16x16x4f64(xs[q][s], bf[t][s], ac[t], 0, 0, 0);
-          }
-          if (st + PF < nst) xload(st + PF, q);
-        }
-      }
-      if (c + 1 < nch) {
-        if (NBUF == 1) __syncthreads();  // every wave is done with the one buffer
-        bstore(c + 1, NBUF == 2 ? buf ^ 1 : 0);
-      }
-      __syncthreads();
+    for (int u = 0; u < EL; ++u) {
+      const int e = min(tid + NTH * u, G * KC - 1), br = e / KC, kk = e % KC;
+      stg[u] = bas[(long)min(g0 + br, N - 1) * a.ldb + min(c * KC + kk, K - 1)];
     }
   };
-  if constexpr (FS) {
-    run(acc, 0, a.kc);
-    if (K > a.kc) run(acc2, a.kc, K - a.kc);  // none at L = 0
-  } else {
-    run(acc, 0, K);
+  auto bstore = [&](int c, int buf) {
+#pragma unroll
+    for (int u = 0; u < EL; ++u) {
+      const int e = tid + NTH * u, br = e / KC, kk = e % KC;
+      if (e < G * KC) sB[buf][br][kk] = keep_if(g0 + br < N && c * KC + kk < K, stg[u]);
+    }
+  };
+  const int nst = (K + 15) / 16, nch = (K + KC - 1) / KC;
+#pragma unroll
+  for (int p = 0; p < PF; ++p) xload(min(p, nst - 1), p);
+  bload(0);
+  __builtin_amdgcn_sched_barrier(0);
+  bstore(0, 0);
+  __syncthreads();
+  for (int c = 0; c < nch; ++c) {
+    const int buf = NBUF == 2 ? (c & 1) : 0;
+    if (c + 1 < nch) bload(c + 1);
+    // the chunk's four stages; stage st = 4c + q sits in register slot q
+#pragma unroll
+    for (int q = 0; q < KC / 16; ++q) {
+      const int st = c * (KC / 16) + q;
+      if (st < nst) {  // uniform
+        double bf[NT][4];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) bf[t][s] = sB[buf][16 * t + lr][slot(q, s)];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            acc[t] = ANA ? __builtin_amdgcn_mfma_f64_16x16x4f64(bf[t][s], xs[q][s], acc[t], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f64_16x16x4f64(xs[q][s], bf[t][s], acc[t], 0, 0, 0);
+        if (st + PF < nst) xload(st + PF, q);
+      }
+    }
+    if (c + 1 < nch) {
+      if (NBUF == 1) __syncthreads();  // every wave is done with the one buffer
+      bstore(c + 1, NBUF == 2 ? buf ^ 1 : 0);
+    }
+    __syncthreads();
   }
   // D layout: lane l, element e -> MFMA row l/16 + 4e, column l%16
 #pragma unroll
@@ -469,24 +407,10 @@ __global__ __launch_bounds__(64 * WAVES) void phi_direct_kernel(PhiDirectArgs a)
     for (int e = 0; e < 4; ++e) {
       if (ANA) {
         const int br = g0 + 16 * t + lg + 4 * e, r = r0 + lr;
-        int mc = br;
-        if constexpr (FA) {
-          const int m = br < a.kc ? br : br - a.kc + 1;
-          mc = br < a.kc ? max(2 * m - 1, 0) : 2 * m;
-        }
-        if (br < N && mc < (FA ? a.nmc : N) && r < M) a.C[(long)mc * ((long)nt * M) + (long)j * M + r] = acc[t][e];
+        if (br < N && r < M) a.C[(long)br * ((long)nt * M) + (long)j * M + r] = acc[t][e];
       } else {
         const int r = r0 + lg + 4 * e, k = g0 + 16 * t + lr;
-        if (r < M && k < N) {
-          double *__restrict__ cr = a.C + (long)r * ((long)nt * np) + (long)j * np;
-          if constexpr (FS) {
-            const double ev = acc[t][e], od = acc2[FS ? t : 0][e];
-            cr[k] = ev + od;
-            if (np - 1 - k != k) cr[np - 1 - k] = ev - od;
-          } else {
-            cr[k] = acc[t][e];
-          }
-        }
+        if (r < M && k < N) a.C[(long)r * ((long)nt * np) + (long)j * np + k] = acc[t][e];
       }
     }
 }
@@ -927,37 +851,22 @@ hipError_t launch_gemm_f64_grouped(int variant, int role, const GemmF64Args *pro
 
 namespace {
 
-template <bool ANA, int WAVES, int NT, int NBUF, bool FOLD>
+template <bool ANA, int WAVES, int NT, int NBUF>
 hipError_t launch_phi_direct_t(const PhiDirectArgs &a, hipStream_t s) {
   dim3 grid((a.M + 16 * WAVES - 1) / (16 * WAVES), a.nt, (a.N + 16 * NT - 1) / (16 * NT));
-  hipLaunchKernelGGL((phi_direct_kernel<ANA, WAVES, NT, NBUF, FOLD>), grid, dim3(64 * WAVES), 0, s, a);
+  hipLaunchKernelGGL((phi_direct_kernel<ANA, WAVES, NT, NBUF>), grid, dim3(64 * WAVES), 0, s, a);
   return hipGetLastError();
 }
 
 template <bool ANA>
 hipError_t launch_phi_direct_v(int variant, const PhiDirectArgs &a, hipStream_t s) {
   switch (variant) {
-    case 0: return launch_phi_direct_t<ANA, 8, 4, 2, false>(a, s);
-    case 1: return launch_phi_direct_t<ANA, 8, 3, 2, false>(a, s);
-    case 2: return launch_phi_direct_t<ANA, 8, 2, 2, false>(a, s);
-    case 3: return launch_phi_direct_t<ANA, 4, 4, 2, false>(a, s);
-    case 4: return launch_phi_direct_t<ANA, 4, 3, 2, false>(a, s);
-    case 5: return launch_phi_direct_t<ANA, 4, 2, 2, false>(a, s);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <bool ANA>
-hipError_t launch_phi_fold_v(int variant, const PhiDirectArgs &a, hipStream_t s) {
-  switch (variant) {
-    case 0: return launch_phi_direct_t<ANA, 2, 4, 1, true>(a, s);
-    case 1: return launch_phi_direct_t<ANA, 4, 4, 1, true>(a, s);
-    case 2: return launch_phi_direct_t<ANA, 8, 4, 1, true>(a, s);
-    case 3: return launch_phi_direct_t<ANA, 2, 5, 1, true>(a, s);
-    case 4: return launch_phi_direct_t<ANA, 4, 5, 1, true>(a, s);
-    case 5: return launch_phi_direct_t<ANA, 8, 5, 1, true>(a, s);
-    case 6: return launch_phi_direct_t<ANA, 4, 4, 2, true>(a, s);
-    case 7: return launch_phi_direct_t<ANA, 4, 5, 2, true>(a, s);
+    case 0: return launch_phi_direct_t<ANA, 8, 4, 2>(a, s);
+    case 1: return launch_phi_direct_t<ANA, 8, 3, 2>(a, s);
+    case 2: return launch_phi_direct_t<ANA, 8, 2, 2>(a, s);
+    case 3: return launch_phi_direct_t<ANA, 4, 4, 2>(a, s);
+    case 4: return launch_phi_direct_t<ANA, 4, 3, 2>(a, s);
+    case 5: return launch_phi_direct_t<ANA, 4, 2, 2>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -968,26 +877,13 @@ hipError_t launch_phi_fold_v(int variant, const PhiDirectArgs &a, hipStream_t s)
 // (measured on MI355X: single-buffered groups of 96-144 basis rows were
 // slower than these at 2L+1 = 51 and n_p = 137)
 const int kPhiDirect[][3] = {{8, 4, 2}, {8, 3, 2}, {8, 2, 2}, {4, 4, 2}, {4, 3, 2}, {4, 2, 2}};
-// the same for the folded form
-const int kPhiFold[][3] = {{2, 4, 1}, {4, 4, 1}, {8, 4, 1}, {2, 5, 1}, {4, 5, 1}, {8, 5, 1}, {4, 4, 2}, {4, 5, 2}};
 
 int phi_direct_variant_count() { return (int)(sizeof(kPhiDirect) / sizeof(kPhiDirect[0])); }
-int phi_fold_variant_count() { return (int)(sizeof(kPhiFold) / sizeof(kPhiFold[0])); }
 
 hipError_t launch_phi_direct(int variant, bool analysis, const PhiDirectArgs &a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.nt <= 0) return hipSuccess;
   if (a.K <= 0 || a.nt > 65535 || (a.N + 31) / 32 > 65535) return hipErrorInvalidValue;
   return analysis ? launch_phi_direct_v<true>(variant, a, s) : launch_phi_direct_v<false>(variant, a, s);
-}
-
-hipError_t launch_phi_fold(int variant, bool analysis, const PhiDirectArgs &a, hipStream_t s) {
-  if (a.M <= 0 || a.N <= 0 || a.nt <= 0) return hipSuccess;
-  if (a.K <= 0 || a.nt > 65535 || (a.N + 31) / 32 > 65535 || a.nmc < 1) return hipErrorInvalidValue;
-  // the cos / sin boundary: whole basis tiles (analysis), whole steps (synthesis)
-  if (a.kc < 0 || a.kc % (analysis ? 16 : 4) != 0) return hipErrorInvalidValue;
-  // analysis: K = h cells of the n_p per row; synthesis: N = h
-  if ((analysis ? a.K : a.N) != (a.np + 1) / 2) return hipErrorInvalidValue;
-  return analysis ? launch_phi_fold_v<true>(variant, a, s) : launch_phi_fold_v<false>(variant, a, s);
 }
 
 namespace {
@@ -1006,6 +902,11 @@ hipError_t launch_phi_syn_lean_t(const PhiLeanArgs &a, hipStream_t s) {
 const int kPhiLean[][2] = {{1, 4}, {1, 8}, {2, 4}, {2, 8}};
 
 int phi_lean_variant_count() { return (int)(sizeof(kPhiLean) / sizeof(kPhiLean[0])); }
+
+int phi_lean_kernel_name(int v, char *buf, size_t n) {
+  if (v < 0 || v >= phi_lean_variant_count()) return -1;
+  return snprintf(buf, n, "yyg::phi_syn_lean_kernel<%d, %d>", kPhiLean[v][0], kPhiLean[v][1]) < 0 ? -1 : 0;
+}
 
 hipError_t launch_phi_syn_lean(int variant, const PhiLeanArgs &a, hipStream_t s) {
   if (a.M <= 0 || a.nt <= 0 || a.h <= 0) return hipSuccess;
@@ -1226,21 +1127,13 @@ int fold_xcol_kernel_name(int v, char *buf, size_t n) {
 }
 
 int sep_kernel_name(int phase, int v, bool fold, char *buf, size_t n) {
-  const int nv = gemm_f64_variant_count(), nd = phi_direct_variant_count(), nf = phi_fold_variant_count();
-  const int nl = phase == 4 ? phi_lean_variant_count() : 0;
+  const int nv = gemm_f64_variant_count(), nd = phi_direct_variant_count();
   const bool phi = phase == 0 || phase == 4;
-  if (phase < 0 || phase > 4 || v < 0 || v >= 2 * nv + (phi ? nd + nf : 0) + nl) return -1;
-  if (v >= 2 * nv + nd + nf) {
-    if (!fold) return -1;
-    const int *d = kPhiLean[v - 2 * nv - nd - nf];
-    return snprintf(buf, n, "yyg::phi_syn_lean_kernel<%d, %d>", d[0], d[1]) < 0 ? -1 : 0;
-  }
+  if (phase < 0 || phase > 4 || v < 0 || v >= 2 * nv + (phi ? nd : 0)) return -1;
   if (v >= 2 * nv) {
-    const bool fd = v >= 2 * nv + nd;
-    if (fd && !fold) return -1;
-    const int *d = fd ? kPhiFold[v - 2 * nv - nd] : kPhiDirect[v - 2 * nv];
-    return snprintf(buf, n, "yyg::phi_direct_kernel<%s, %d, %d, %d, %s>", phase == 0 ? "true" : "false", d[0], d[1],
-                    d[2], fd ? "true" : "false") < 0 ? -1 : 0;
+    const int *d = kPhiDirect[v - 2 * nv];
+    return snprintf(buf, n, "yyg::phi_direct_kernel<%s, %d, %d, %d>", phase == 0 ? "true" : "false", d[0], d[1],
+                    d[2]) < 0 ? -1 : 0;
   }
   const F64Variant &f = kF64Variants[v % nv];
   const int deep = v >= nv ? kGemmDeep : 0;
