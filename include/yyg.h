@@ -315,7 +315,11 @@ int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n);
  * patch's moments (Yin-Yang grids; no work on a polar grid), 3 theta
  * synthesis, 4 phi synthesis.  variant in [0, 2V), V = the number of FP64
  * tile variants: V + v is tile v with three stages of operand loads in
- * flight instead of one; the phi phases also take [2V, 2V + 6), kernels
+ * flight instead of one (in phases 1-3, up to lmax 94 and where the tables
+ * fit, V + 4 and V + 5 are kernels that load their operands straight from
+ * memory, the theta transforms folded about the equator and the rotation
+ * split by parity, which a plan starts from); the phi phases also take
+ * [2V, 2V + 6), kernels
  * that keep the phi basis in LDS and stream the data straight into MFMA
  * fragments (unfolded), and [2V + 6, 2V + 14), kernels folded about the
  * patch's central meridian and, on a grid that is symmetric about them

@@ -187,6 +187,11 @@ struct yyg_grid {
     yyg::PhiLeanArgs phi_syn_l{};
     // theta phases and rotation: one launch each over their problems
     yyg::SepPhaseArgs args{};
+    // the same three with their operands straight from memory (stream[r]:
+    // phase r = 1..3 can run so on this plan)
+    yyg::ThetaArgs theta{};
+    bool stream[4] = {false, false, false, false};
+    double *TA = nullptr, *TS = nullptr, *DR = nullptr;  // folded theta bases, rotation blocks by class
     // variant per phase (0 phi analysis, 1 theta analysis, 2 moment
     // rotation, 3 theta synthesis, 4 phi synthesis): v < V the tile v,
     // V + v the same with the deep prefetch, 2V + d (phi phases) the
@@ -215,7 +220,7 @@ hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 void sep_release(yyg_grid *g) {
   auto &S = g->sep;
   double **b[] = {&S.Wcs, &S.trig, &S.T2, &S.P2, &S.Drot, &S.X2, &S.V,   &S.Ut,  &S.coefS,
-                  &S.At,  &S.WF,   &S.TF, &S.QA, &S.QS, &S.QW, &S.BK, &S.WFAB, &S.CSF, &S.Wt};
+                  &S.At,  &S.WF,   &S.TF, &S.QA, &S.QS, &S.QW, &S.TA, &S.TS, &S.DR, &S.BK, &S.WFAB, &S.CSF, &S.Wt};
   for (double **x : b) {
     if (*x) (void)dev_free(*x);
     *x = nullptr;
@@ -409,8 +414,20 @@ int sep_set_variant(yyg_grid *g, int r, int v) {
   return YYG_OK;
 }
 
+// Variants V + 4 and V + 5 of phases 1-3 (the two largest tiles with three
+// stages in flight, far wider than these problems) run the kernels of
+// yyg_theta.hip where the plan allows.
+int sep_theta_variant(const yyg_grid *g, int r, int v) {
+  const int u = v - yyg::gemm_f64_variant_count() - 4;
+  return r >= 1 && r <= 3 && (u == 0 || u == 1) && g->sep.stream[r] ? u : -1;
+}
+
 hipError_t sep_launch_phase(yyg_grid *g, int r, hipStream_t s) {
   auto &S = g->sep;
+  if (const int u = sep_theta_variant(g, r, S.var[r]); u >= 0) {
+    if (r == 2 && g->n_patch != 2) return hipSuccess;
+    return yyg::launch_theta_stream(r, u, S.theta, g->cus, s);
+  }
   const int nv = yyg::gemm_f64_variant_count(), nd = yyg::phi_direct_variant_count();
   const int nf = yyg::phi_quad_variant_count();
   if (r == 4 && S.var[r] >= sep_stream_base(4))
@@ -466,6 +483,11 @@ void sep_bind_work(yyg_grid *g, const SepWork &w) {
   S.args.Ahat = w.Ahat;
   S.args.At = w.At;
   S.args.V = w.V;
+  S.theta.X2 = w.X2;
+  S.theta.Ut = w.Ut;
+  S.theta.Ahat = w.Ahat;
+  S.theta.At = w.At;
+  S.theta.V = w.V;
 }
 
 // Doubles of the separable form's work buffers, each region rounded up to
@@ -579,6 +601,88 @@ void sep_quad_tables(yyg_grid *g, const std::vector<double> &CSt, const std::vec
   }
 }
 
+// Folded bases of the theta phases (yyg::ThetaArgs) from the tables T and P
+// [j][q], and which of phases 1-3 can run from memory: the theta phases where
+// the tables show the parity (-1)^(l + m) about the equator to 1e-12 of
+// their largest entry, the rotation where D_l vanishes outside the parity
+// classes to 1e-12 (its entries are at most 1), each where its kernel holds
+// the degree.
+void sep_theta_tables(yyg_grid *g, const std::vector<double> &T, const std::vector<double> &P,
+                      const std::vector<double> &D, std::vector<double> &TA, std::vector<double> &TS,
+                      std::vector<double> &DR) {
+  auto &S = g->sep;
+  const int L = g->L, Q = g->Q, nt = g->n_t, h = (nt + 1) / 2;
+  auto odd = [&](const std::vector<double> &X) {
+    double top = 0.0, bad = 0.0;
+    for (double v : X) top = std::max(top, std::fabs(v));
+    for (int l = 0; l <= L; ++l)
+      for (int m = 0; m <= l; ++m) {
+        const int q = l * l + (m ? 2 * m : 0);
+        const double sg = (l + m) % 2 ? -1.0 : 1.0;
+        for (int j = 0; j < h; ++j)
+          bad = std::max(bad, std::fabs(X[(size_t)j * Q + q] - sg * X[(size_t)(nt - 1 - j) * Q + q]));
+      }
+    return bad > 1e-12 * top;
+  };
+  S.stream[1] = yyg::theta_stream_fits(1, L, h) && !odd(T);
+  S.stream[3] = yyg::theta_stream_fits(3, L, h) && !odd(P);
+  S.stream[2] = g->n_patch == 2 && yyg::theta_stream_fits(2, L, h);
+  // the class of a column within its degree (cos / sin, parity of m), the
+  // class of the other patch it takes, a class's members
+  auto cls = [](int b) {
+    const int m = (b + 1) / 2;
+    return b > 0 && b % 2 == 0 ? 2 + m % 2 : m % 2;
+  };
+  auto from = [](int l, int c) { return l % 2 ? (c == 0 ? 3 : c == 3 ? 0 : c) : (c == 1 ? 2 : c == 2 ? 1 : c); };
+  auto member = [](int c, int i) { return c == 0 ? std::max(4 * i - 1, 0) : c == 1 ? 4 * i + 1 : c == 2 ? 4 * i + 4 : 4 * i + 2; };
+  auto members = [](int l, int c) { return c == 0 ? l / 2 + 1 : c == 2 ? l / 2 : (l + 1) / 2; };
+  size_t off = 0;
+  for (int l = 0; l <= L && S.stream[2]; ++l) {
+    const int d = 2 * l + 1;
+    for (int k = 0; k < d; ++k)
+      for (int b = 0; b < d; ++b)
+        if (cls(k) != from(l, cls(b)) && std::fabs(D[off + (size_t)k * d + b]) > 1e-12) S.stream[2] = false;
+    off += (size_t)d * d;
+  }
+  DR.clear();
+  if (S.stream[2]) {
+    const size_t std_ = yyg::rotation_doubles(L);
+    DR.assign((size_t)4 * (L + 1) * std_, 0.0);
+    off = 0;
+    for (int l = 0; l <= L; ++l) {
+      const int d = 2 * l + 1;
+      for (int c = 0; c < 4; ++c) {
+        const int nb = members(l, c), kq = (nb + 3) / 4;
+        for (int i = 0; i < nb; ++i)
+          for (int k = 0; k < nb; ++k)
+            DR[(4 * (size_t)l + c) * std_ + ((size_t)(i / 16) * kq + k / 4) * 64 + 16 * (k % 4) + i % 16] =
+                D[off + (size_t)member(from(l, c), k) * d + member(c, i)];
+      }
+      off += (size_t)d * d;
+    }
+  }
+  const size_t sta = yyg::theta_ana_doubles(L, h), sts = yyg::theta_syn_doubles(L, h);
+  TA.clear();
+  TS.clear();
+  if (S.stream[1]) TA.assign((size_t)(L + 1) * sta, 0.0);
+  if (S.stream[3]) TS.assign((size_t)(L + 1) * sts, 0.0);
+  for (int m = 0; m <= L; ++m) {
+    const int t1 = ((L - m) / 2 + 16) / 16, kp = ((L - m) / 2 + 8) / 8;
+    for (int l = m; l <= L; ++l) {
+      const int par = (l - m) % 2, i = (l - m) / 2, q = l * l + (m ? 2 * m : 0);
+      for (int j = 0; j < h; ++j) {
+        const int qa = j / 4, qs = i / 4;
+        if (S.stream[1])
+          TA[m * sta + (((size_t)(qa / 2) * 2 + par) * t1 + i / 16) * 128 + 2 * (16 * (j % 4) + i % 16) + qa % 2] =
+              (nt - 1 - j == j ? 0.5 : 1.0) * T[(size_t)j * Q + q];
+        if (S.stream[3])
+          TS[m * sts + (((size_t)(j / 16) * kp + qs / 2) * 2 + par) * 128 + 2 * (16 * (i % 4) + j % 16) + qs % 2] =
+              P[(size_t)j * Q + q];
+      }
+    }
+  }
+}
+
 // Default kernels of the phi phases on a folded grid.
 void sep_default_phi(yyg_grid *g) {
   auto &S = g->sep;
@@ -600,7 +704,7 @@ int sep_build(yyg_grid *g) {
   S.ldm = round_up(nmc, 16);
   S.ldl = round_up(L + 1, 16);
   if (!yyg::radial_scan_q_supports(g->n_r, g->n_patch)) return YYG_ERR_UNSUPPORTED;
-  std::vector<double> CSt, Wcs, trig, T, P, T2, P2, D, coef, coefS, WF, TF, BK, WFAB, CSF, WTF, QA, QS, QW;
+  std::vector<double> CSt, Wcs, trig, T, P, T2, P2, D, coef, coefS, WF, TF, BK, WFAB, CSF, WTF, QA, QS, QW, TA, TS, DR;
   int nte = 0, nto = 0, ldcs = 0;
   try {
     coef.resize((size_t)4 * g->n_r * (L + 1));
@@ -733,6 +837,7 @@ int sep_build(yyg_grid *g) {
     // patch's own moments and adds the other patch's moments times D_l)
     D.resize(yyg::rotation_blocks_size(L));
     yyg::rotation_blocks(L, D.data());
+    sep_theta_tables(g, T, P, D, TA, TS, DR);
   } catch (const std::bad_alloc &) {
     return YYG_ERR_OUT_OF_MEMORY;
   }
@@ -749,6 +854,9 @@ int sep_build(yyg_grid *g) {
   if (st == YYG_OK) st = dmalloc(&S.coefS, coefS.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.WF, WF.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.TF, TF.size());
+  if (st == YYG_OK && !TA.empty()) st = dmalloc(&S.TA, TA.size());
+  if (st == YYG_OK && !TS.empty()) st = dmalloc(&S.TS, TS.size());
+  if (st == YYG_OK && !DR.empty()) st = dmalloc(&S.DR, DR.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.QA, QA.size());
   if (st == YYG_OK && S.fold) st = dmalloc(&S.QS, QS.size());
   if (st == YYG_OK && !QW.empty()) st = dmalloc(&S.QW, QW.size());
@@ -766,6 +874,9 @@ int sep_build(yyg_grid *g) {
   };
   chk(hipMemcpy(S.Wcs, Wcs.data(), Wcs.size() * sizeof(double), hipMemcpyHostToDevice));
   chk(hipMemcpy(S.trig, trig.data(), trig.size() * sizeof(double), hipMemcpyHostToDevice));
+  if (S.TA) chk(hipMemcpy(S.TA, TA.data(), TA.size() * sizeof(double), hipMemcpyHostToDevice));
+  if (S.TS) chk(hipMemcpy(S.TS, TS.data(), TS.size() * sizeof(double), hipMemcpyHostToDevice));
+  if (S.DR) chk(hipMemcpy(S.DR, DR.data(), DR.size() * sizeof(double), hipMemcpyHostToDevice));
   chk(hipMemcpy(S.T2, T2.data(), T2.size() * sizeof(double), hipMemcpyHostToDevice));
   chk(hipMemcpy(S.P2, P2.data(), P2.size() * sizeof(double), hipMemcpyHostToDevice));
   chk(hipMemcpy(S.Drot, D.data(), D.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -846,6 +957,11 @@ int sep_build(yyg_grid *g) {
   // operands derived in the kernels from these
   S.args = yyg::SepPhaseArgs{L,    g->n_r, g->n_patch, nt,  S.ldl, S.X2, S.T2, S.P2,
                              S.Ut, S.Drot,   g->d_Ahat,  S.At, S.V};
+  S.theta = yyg::ThetaArgs{S.X2,     S.TA, S.TS, S.Ut, S.DR, g->d_Ahat, S.At, S.V,
+                           MJ,       (long)yyg::theta_ana_doubles(L, (nt + 1) / 2),
+                           (long)yyg::theta_syn_doubles(L, (nt + 1) / 2), (long)yyg::rotation_doubles(L), L, g->n_r, (int)M, nt, (nt + 1) / 2};
+  for (int r = 1; r <= 3; ++r)
+    if (S.stream[r]) S.var[r] = yyg::gemm_f64_variant_count() + 4;
   S.ready = true;
   return YYG_OK;
 }
@@ -2214,6 +2330,8 @@ int yyg_sep_kernel(const yyg_grid *g, int phase, char *name, size_t n) {
                     ? yyg::phi_ana_stream_kernel_name(v - sep_stream_base(0), name, n)
                 : v >= x0                    ? yyg::x4_kernel_name(v - x0, phase, g->sep.fold, name, n)
                 : phase == 4 && v >= lean    ? yyg::phi_lean_kernel_name(v - lean, name, n)
+                : sep_theta_variant(g, phase, v) >= 0
+                    ? yyg::theta_stream_kernel_name(phase, sep_theta_variant(g, phase, v), g->sep.theta, name, n)
                 : !sep_fold_variant(phase, v) ? yyg::sep_kernel_name(phase, v, g->sep.fold, name, n)
                                              : yyg::phi_quad_kernel_name(v - quad, phase == 0,
                                                                          phase == 0 ? g->sep.quad_ana : g->sep.quad_syn,

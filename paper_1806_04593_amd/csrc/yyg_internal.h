@@ -189,6 +189,32 @@ hipError_t launch_x4_sep_phase(int variant, int phase, bool fold, const GemmF64A
                                const SepPhaseArgs &a, hipStream_t s);
 int x4_kernel_name(int variant, int phase, bool fold, char *buf, size_t n);
 
+// The theta transforms folded about the equator and the rotation by parity
+// class, operands loaded straight from memory (yyg_theta.hip); phases 1, 3
+// and 2.  TA / TS hold the folded bases per order m, sta / sts doubles apart:
+//  TA [pair of steps][l + m even / odd][tile][lane][2]: lane (g, o) has
+//     degree m + parity + 2 (16 tile + o) at colatitude 4 q + g, q = 2 pair +
+//     {0, 1}, a middle row halved, with ((L - m) / 2 + 16) / 16 tiles;
+//  TS [tile of 16 colatitudes][pair][parity][lane][2]: lane (g, o) has
+//     colatitude 16 tile + o at degree m + parity + 2 (4 q + g);
+// zero past h = ceil(n_t / 2) and past L;
+//  DR per degree and class c, std doubles each: the block of D_l from the
+//     other patch's class to c, [tile][step][lane]: lane (g, o) has member
+//     16 tile + o of c from member 4 step + g (ceil(n / 16) tiles of
+//     ceil(n / 4) steps, n the members; zero past them).
+struct ThetaArgs {
+  const double *X2, *TA, *TS, *Ut, *DR;
+  double *Ahat, *At, *V;
+  long MJ, sta, sts, std;
+  int L, nR, Mr, nt, h;
+};
+size_t theta_ana_doubles(int L, int h);  // sta: a block's LDS too
+size_t theta_syn_doubles(int L, int h);  // sts
+size_t rotation_doubles(int L);          // std
+bool theta_stream_fits(int phase, int L, int h);
+hipError_t launch_theta_stream(int phase, int variant, const ThetaArgs &a, int cus, hipStream_t s);
+int theta_stream_kernel_name(int phase, int variant, const ThetaArgs &a, char *buf, size_t n);
+
 // phase 1 theta analysis, 2 rotation (two patches), 3 theta synthesis;
 // deep = kGemmDeep.
 hipError_t launch_gemm_f64_sep(int variant, int phase, bool deep, const SepPhaseArgs &a, hipStream_t s);
