@@ -138,7 +138,11 @@ int yyg_prepare(yyg_grid *g, int precision);
  *  YYG_METHOD_DENSE      the two angular contractions as dense MFMA
  *                        contractions over all angular cells (Eqs. 26-27 and
  *                        5, 28-29 written as matrix products): 2Q + 4Q flops
- *                        per cell.
+ *                        per cell.  FP64 from degree 2 on and about 4e6
+ *                        products contracts over a quarter of the patch, by
+ *                        the two mirror symmetries: a quarter of that, for
+ *                        one density-sized buffer and a quarter of the bases
+ *                        more memory (unfolded where that is not to be had).
  *  YYG_METHOD_SEPARABLE  the same sums factored along the tensor structure
  *                        of the tables: the analysis as a transform over phi
  *                        (w_jk C/S_k^(m), a GEMM per colatitude row) followed
@@ -294,7 +298,8 @@ int yyg_get_timing(yyg_grid *g, double *ms, long *counts, int n_slots);
  * or BF16 x 3: the tile shape of the reduced-precision phi transforms.  Allocates scratch memory for the
  * duration of the call and may grow the plan's partial-moment buffer.  With
  * the environment variable YYG_TUNE_CACHE naming a file, earlier choices
- * for the same (precision, shape) are read from it and new ones appended.
+ * for the same (precision, shape) are read from it and new ones appended. A
+ * folded dense plan's shape is that of its quarter patch.
  * Without autotuning a plan uses a fixed heuristic.  Results do not depend
  * on the choice beyond FP64 summation order. */
 int yyg_autotune(yyg_grid *g, int precision, void *stream);

@@ -117,6 +117,23 @@ struct yyg_grid {
   bool ahat_cols = false;    // d_Ahat holds the column-major layout
   double *d_U = nullptr;     // synthesis operand [P n_r][ldy]
   double *d_rho_owned = nullptr;
+  bool ahat_fold = false;  // d_Ahat's columns are in the fold's order
+
+  // dense FP64 solve folded about both mirror planes (yyg_dense_fold.hip);
+  // class c holds columns cols[co[c] .. co[c] + N[c])
+  struct Fold {
+    bool ready = false;
+    long hq = 0;             // cells of a quarter patch
+    long ldb = 0, ldy[4] = {};
+    int N[4] = {}, co[4] = {};  // columns of a class, first one
+    int K[4] = {}, ko[4] = {};  // synthesis contraction length of a class, first column in U
+    std::vector<int> cols;   // column q at each place
+    int *d_cols = nullptr, *d_deg = nullptr;
+    int2 *d_ucol = nullptr;
+    double *Bt = nullptr;    // [Q][ldb]
+    double *Y[4] = {};       // [hq][ldy[c]]
+    double *F = nullptr;     // folded densities, then the classes' potentials [4][P n_r][hq]
+  } fold;
   int cus = 256;  // compute units of the device (persistent grids)
   // opt-in check of the density for NaN / infinity before each solve
   bool check_finite = false;
@@ -238,8 +255,17 @@ void lp_release(LpPlan &l) {
   }
 }
 
+void fold_release(yyg_grid *g) {
+  auto &f = g->fold;
+  void *b[] = {f.d_cols, f.d_deg, f.d_ucol, f.Bt, f.Y[0], f.Y[1], f.Y[2], f.Y[3], f.F};
+  for (void *x : b)
+    if (x) (void)dev_free(x);
+  f = yyg_grid::Fold{};
+}
+
 void free_grid(yyg_grid *g) {
   if (!g) return;
+  fold_release(g);
   double *bufs[] = {g->d_Bt, g->d_Y, g->d_coef, g->d_part, g->d_Ahat, g->d_U, g->d_rho_owned};
   (void)dev_free(g->d_flag);
   for (double *b : bufs)
@@ -332,6 +358,149 @@ double time_launch(F launch, hipStream_t s, int reps) {
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
   return best;
+}
+
+// Cells of the quarter patch.
+long fold_cells(const yyg_grid *g) { return (long)((g->n_t + 1) / 2) * ((g->n_p + 1) / 2); }
+
+// Columns of class c: the degrees l = m, m + 2, .. (odd: m + 1, ..) of its orders.
+int fold_columns(int L, int c) {
+  int n = 0;
+  for (int m = c & 1; m <= L; ++m) n += c & 2 ? (L - m + 1) / 2 : (L - m) / 2 + 1;
+  return n;
+}
+
+// Tiles of the four analysis contractions.
+long fold_analysis_tiles(const yyg_grid *g, int bm, int bn) {
+  const long M = (long)g->n_patch * g->n_r;
+  long t = 0;
+  for (int c = 0; c < 4; ++c) t += ((M + bm - 1) / bm) * ((fold_columns(g->L, c) + bn - 1) / bn);
+  return t;
+}
+
+// Tile shapes and split of a new plan's folded contractions: 64 x 64 tiles of
+// eight waves (variant 11), and 32 x 32 (variant 10) where those pad the
+// product by over a tenth more, or give the synthesis under four tiles a CU.
+// Measured (fold, contraction and scan; contraction and unfold): 2 degrees,
+// 400 shells, degree 25: 64-wide 87 and 100 us, 32-wide 87 and 102, 128-wide
+// 118 and 135; 4 degrees, 100 shells, degree 12: 29 and 13, 27 and 12, 42 and
+// 30; 1 degree, 100 shells, degree 40 (rows pad by 1.14): 155 and 249, 151
+// and 233, 187 and 297.  The split of 64-wide tiles is at least 2 over long
+// contractions, where one wave of blocks leaves the last CUs idle.
+void fold_shape(const yyg_grid *g, int *var_ana, int *var_syn, int *nsplit) {
+  const long M = (long)g->n_patch * g->n_r, hq = fold_cells(g);
+  const auto pad = [](long n, long b) { return (n + b - 1) / b * b; };
+  const double rows = (double)pad(M, 64) / pad(M, 32);
+  const long t64 = fold_analysis_tiles(g, 64, 64), t32 = fold_analysis_tiles(g, 32, 32);
+  *var_ana = 4.0 * t64 <= 1.1 * t32 ? 11 : 10;
+  *var_syn = rows * pad(hq, 64) / pad(hq, 32) <= 1.1 && 4 * (pad(M, 64) / 64) * (pad(hq, 64) / 64) >= 4L * g->cus ? 11 : 10;
+  *nsplit = yyg::choose_split(*var_ana == 11 ? t64 : t32, hq);
+  if (*var_ana == 11 && hq >= 1024) *nsplit = std::max(*nsplit, 2);
+}
+
+// Whether the dense FP64 solve of this plan is to run folded: a column in every
+// class (L >= 2), rows within a launch's reach, and work enough to pay for two
+// more launches (tuned plans: 1.0e6 products 22.7 us folded against 19.0,
+// 1.2e7 26.4 against 30.0).
+constexpr double kFoldMinMacs = 4e6;
+bool fold_wanted(const yyg_grid *g) {
+  const long M = (long)g->n_patch * g->n_r;
+  return g->L >= 2 && M <= 65535 && (double)M * g->nang * g->Q * (1 + g->n_patch) >= kFoldMinMacs;
+}
+
+// The fold's tables.  False (not wanted, memory short, or a table without the
+// symmetry): the plan solves unfolded.
+bool fold_build(yyg_grid *g) {
+  auto &f = g->fold;
+  const int Q = g->Q, P = g->n_patch;
+  const long M = (long)P * g->n_r;
+  if (!fold_wanted(g)) return false;
+  f.hq = fold_cells(g);
+  f.ldb = round_up(f.hq, 16);
+  std::vector<int> deg, ycols;
+  std::vector<int2> ucol;
+  int yo[4];
+  const auto swapped = [](int c) { return (c >> 1) | (c & 1) << 1; };
+  try {
+    const auto tab = yyg::column_table(g->L);
+    for (int c = 0; c < 4; ++c) {
+      f.co[c] = (int)f.cols.size();
+      for (int q = 0; q < Q; ++q)
+        if ((((tab[q].l + tab[q].m) & 1) << 1 | (tab[q].is_sin ? 1 : 0)) == c) f.cols.push_back(q);
+      f.N[c] = (int)f.cols.size() - f.co[c];
+    }
+    for (int c = 0, at = 0; c < 4; at += f.K[c++]) {
+      f.ko[c] = at;
+      f.K[c] = f.N[c] + (P == 2 ? f.N[swapped(c)] : 0);
+      f.ldy[c] = round_up(f.K[c], 16);
+      yo[c] = (int)ycols.size();
+      for (int i = 0; i < f.N[c]; ++i) ycols.push_back(f.cols[f.co[c] + i]);
+      for (int i = 0; P == 2 && i < f.N[swapped(c)]; ++i) ycols.push_back(Q + f.cols[f.co[swapped(c)] + i]);
+    }
+    for (int c = 0; c < 4; ++c)
+      for (int i = 0; i < f.N[c]; ++i) {
+        deg.push_back(tab[f.cols[f.co[c] + i]].l);
+        ucol.push_back(int2{f.ko[c] + i, f.ko[swapped(c)] + f.N[swapped(c)] + i});
+      }
+  } catch (const std::bad_alloc &) {
+    return false;
+  }
+  int *d_ycols = nullptr, *d_flag = nullptr;
+  int st = dmalloc(&f.d_cols, (size_t)Q);
+  if (st == YYG_OK) st = dmalloc(&f.d_deg, (size_t)Q);
+  if (st == YYG_OK) st = dmalloc(&f.d_ucol, (size_t)Q);
+  if (st == YYG_OK) st = dmalloc(&f.Bt, (size_t)Q * f.ldb);
+  for (int c = 0; c < 4 && st == YYG_OK; ++c) st = dmalloc(&f.Y[c], (size_t)f.hq * f.ldy[c]);
+  if (st == YYG_OK) st = dmalloc(&f.F, (size_t)4 * M * f.hq);
+  if (st == YYG_OK) st = dmalloc(&d_ycols, ycols.size());
+  if (st == YYG_OK) st = dmalloc(&d_flag, 1);
+  hipError_t e = st == YYG_OK ? hipSuccess : hipErrorOutOfMemory;
+  auto chk = [&](hipError_t r) {
+    if (e == hipSuccess && r != hipSuccess) e = r;
+  };
+  int bad = 0;
+  if (e == hipSuccess) {
+    chk(hipMemcpy(f.d_cols, f.cols.data(), Q * sizeof(int), hipMemcpyHostToDevice));
+    chk(hipMemcpy(f.d_deg, deg.data(), Q * sizeof(int), hipMemcpyHostToDevice));
+    chk(hipMemcpy(f.d_ucol, ucol.data(), Q * sizeof(int2), hipMemcpyHostToDevice));
+    chk(hipMemcpy(d_ycols, ycols.data(), ycols.size() * sizeof(int), hipMemcpyHostToDevice));
+    chk(hipMemcpy(d_flag, &bad, sizeof(int), hipMemcpyHostToDevice));
+    for (int c = 0; c < 4 && e == hipSuccess; ++c) {
+      chk(yyg::launch_fold_analysis_basis(g->d_Bt, g->ldb, f.d_cols + f.co[c], f.N[c], c, g->n_t, g->n_p,
+                                          f.Bt + f.co[c] * f.ldb, f.ldb, d_flag, 0));
+      chk(yyg::launch_fold_synthesis_basis(g->d_Y, g->ldy, d_ycols + yo[c], f.K[c], c, g->n_t, g->n_p, f.Y[c],
+                                           f.ldy[c], d_flag, 0));
+    }
+    chk(hipMemcpy(&bad, d_flag, sizeof(int), hipMemcpyDeviceToHost));
+  }
+  if (d_ycols) (void)dev_free(d_ycols);
+  if (d_flag) (void)dev_free(d_flag);
+  if (e != hipSuccess) (void)hipGetLastError();
+  f.ready = e == hipSuccess && bad == 0;
+  return f.ready;
+}
+
+// The four classes' analysis contractions over the folded densities in F;
+// part [nsplit][M][Q], columns in the fold's order.
+hipError_t fold_analysis(yyg_grid *g, int variant, int nsplit, double *part, hipStream_t s) {
+  const auto &f = g->fold;
+  const long M = (long)g->n_patch * g->n_r;
+  yyg::GemmF64Quad q{};
+  for (int c = 0; c < 4; ++c)
+    q.g[c] = yyg::GemmF64Args{(int)M, f.N[c], (int)f.hq, f.F + c * M * f.hq, f.hq, f.Bt + f.co[c] * f.ldb, f.ldb,
+                              part + f.co[c], g->Q, M * g->Q, 0, 0};
+  return yyg::launch_gemm_f64_quad(variant, 0, q, nsplit, s);
+}
+
+// The four classes' potentials on the quarter patch, into F.
+hipError_t fold_synthesis(yyg_grid *g, int variant, hipStream_t s) {
+  const auto &f = g->fold;
+  const long M = (long)g->n_patch * g->n_r;
+  yyg::GemmF64Quad q{};
+  for (int c = 0; c < 4; ++c)
+    q.g[c] = yyg::GemmF64Args{(int)M, (int)f.hq, f.K[c], g->d_U + f.ko[c], g->ldy, f.Y[c], f.ldy[c],
+                              f.F + c * M * f.hq, f.hq, 0, 0, 0};
+  return yyg::launch_gemm_f64_quad(variant, 1, q, 1, s);
 }
 
 std::string tune_key(int prec, int role, long M, long N, long K) {
@@ -1022,6 +1191,7 @@ hipError_t sep_solve(yyg_grid *g, hipStream_t s, int precision = YYG_FP64) {
   auto &S = g->sep;
   hipError_t e = hipSuccess;
   g->ahat_cols = true;
+  g->ahat_fold = false;
   int t = timing_begin(g, 4, s);
   e = sep_launch_phi(g, 0, precision, s);
   timing_end(g, t, s);
@@ -1497,11 +1667,16 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
                                       : yyg::make_patch(g->n_t, g->n_p, d->delta_theta, d->delta_phi);
   const int L = g->L, Q = g->Q, n_r = g->n_r;
   const long M = (long)g->n_patch * n_r;
+  int fold_split = 1, fold_ana = 0, fold_syn = 0;
   {
     int bm, bn;
     yyg::gemm_f64_variant_tile(g->var_ana, &bm, &bn);
     g->nsplit = yyg::choose_split(((M + bm - 1) / bm) * ((Q + bn - 1) / bn), g->nang);
     g->part_cap = g->nsplit;
+    if (fold_wanted(g)) {
+      fold_shape(g, &fold_ana, &fold_syn, &fold_split);
+      g->part_cap = std::max(g->part_cap, fold_split);
+    }
   }
 
   std::vector<double> Tt, CS, coef, P, Tr, Yx;
@@ -1556,7 +1731,7 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
   if (st == YYG_OK) st = dmalloc(&g->d_Y, (size_t)g->nang * g->ldy);
   if (st == YYG_OK) st = dmalloc(&g->d_coef, coef.size());
   if (st == YYG_OK) st = dmalloc(&g->d_qdeg, (size_t)Q);
-  if (st == YYG_OK) st = dmalloc(&g->d_part, (size_t)g->nsplit * M * Q);
+  if (st == YYG_OK) st = dmalloc(&g->d_part, (size_t)g->part_cap * M * Q);
   if (st == YYG_OK) st = dmalloc(&g->d_Ahat, (size_t)M * Q);
   if (st == YYG_OK) st = dmalloc(&g->d_U, (size_t)M * g->ldy);
   if (st == YYG_OK) st = dmalloc(&d_w, (size_t)g->nang);
@@ -1594,6 +1769,12 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
     (void)hipGetLastError();
     free_grid(g);
     return YYG_ERR_DEVICE;
+  }
+  if (!fold_build(g)) fold_release(g);  // the unfolded solve runs instead
+  if (g->fold.ready) {
+    g->nsplit = fold_split;
+    g->var_ana = fold_ana;
+    g->var_syn = fold_syn;
   }
   *out = g;
   return YYG_OK;
@@ -1772,6 +1953,8 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
     return YYG_OK;
   }
   g->ahat_cols = false;
+  const bool fold = !lp && g->fold.ready;
+  g->ahat_fold = fold;
   const int nsplit = lp ? g->lp[precision - 1].nsplit : g->nsplit;
   if (lp) {
     // split the density into operand planes (rows scaled for FP16)
@@ -1785,7 +1968,10 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
   }
   if (e == hipSuccess) {
     t = timing_begin(g, 0, s);
-    if (!lp) {
+    if (fold) {
+      e = yyg::launch_fold_rows(g->rho, g->fold.F, (int)M, g->n_t, g->n_p, s);
+      if (e == hipSuccess) e = fold_analysis(g, g->var_ana, nsplit, g->d_part, s);
+    } else if (!lp) {
       e = yyg::launch_gemm_nt_f64(g->var_ana, 0, (int)M, Q, (int)g->nang, g->rho, g->nang, g->d_Bt, g->ldb,
                                   g->d_part, Q, nsplit, M * Q, s);
     } else {
@@ -1798,8 +1984,8 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
   }
   if (e == hipSuccess) {
     t = timing_begin(g, 1, s);
-    e = yyg::launch_radial_scan(g->d_part, nsplit, M * Q, g->d_Ahat, g->d_coef, g->d_qdeg, n_r, Q, g->L, -g->G,
-                                g->d_U, g->ldy, g->n_patch, s);
+    e = yyg::launch_radial_scan(g->d_part, nsplit, M * Q, g->d_Ahat, g->d_coef, fold ? g->fold.d_deg : g->d_qdeg, n_r,
+                                Q, g->L, -g->G, g->d_U, g->ldy, g->n_patch, s, fold ? g->fold.d_ucol : nullptr);
     timing_end(g, t, s);
   }
   if (e == hipSuccess && lp) {
@@ -1813,7 +1999,10 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
   }
   if (e == hipSuccess) {
     t = timing_begin(g, 2, s);
-    if (!lp) {
+    if (fold) {
+      e = fold_synthesis(g, g->var_syn, s);
+      if (e == hipSuccess) e = yyg::launch_unfold_rows(g->fold.F, out, (int)M, g->n_t, g->n_p, s);
+    } else if (!lp) {
       e = yyg::launch_gemm_nt_f64(g->var_syn, 1, (int)M, (int)g->nang, g->n_patch * Q, g->d_U, g->ldy, g->d_Y, g->ldy, out,
                                   g->nang, 1, 0, s);
     } else {
@@ -1863,7 +2052,7 @@ int yyg_solve_noalloc(yyg_grid *g, const double *rho, double *phi, void *stream)
   w.At = g->n_patch == 2 ? p : nullptr, p += g->n_patch == 2 ? r32(M * g->Q) : 0;
   w.Ahat = p;
   const SepWork own = sep_work(g);
-  const bool timing = g->timing, cols = g->ahat_cols;
+  const bool timing = g->timing, cols = g->ahat_cols, folded = g->ahat_fold;
   g->timing = false;  // no events: nothing is created
   sep_bind_work(g, w);
   hipStream_t s = as_stream(stream);
@@ -1872,6 +2061,7 @@ int yyg_solve_noalloc(yyg_grid *g, const double *rho, double *phi, void *stream)
   if (e == hipSuccess) e = sep_solve(g, s);
   sep_bind_work(g, own);
   g->timing = timing;
+  g->ahat_fold = folded;
   g->ahat_cols = cols;  // the plan's moments buffer still holds the last yyg_solve's
   sep_set_pointers(g, nullptr, nullptr, s);
   if (e != hipSuccess) {
@@ -1913,6 +2103,12 @@ int yyg_get_moments(yyg_grid *g, double *A_host) {
     std::vector<double> t(A_host, A_host + M * g->Q);
     for (long r = 0; r < M; ++r)
       for (int q = 0; q < g->Q; ++q) A_host[r * g->Q + q] = t[q * M + r];
+  } else if (g->ahat_fold) {
+    std::vector<double> t(g->Q);
+    for (long r = 0; r < M; ++r) {
+      std::copy(A_host + r * g->Q, A_host + (r + 1) * g->Q, t.begin());
+      for (int n = 0; n < g->Q; ++n) A_host[r * g->Q + g->fold.cols[n]] = t[n];
+    }
   }
   for (long r = 0; r < M; ++r)
     for (int q = 0; q < g->Q; ++q) A_host[r * g->Q + q] /= g->nrm_q[q];
@@ -2049,7 +2245,10 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
   };
   const char *cache_path = std::getenv("YYG_TUNE_CACHE");
   auto cache = read_tune_cache(cache_path);
-  const std::string ka = tune_key(precision, 0, M, Q, g->nang), ks = tune_key(precision, 1, M, g->nang, (long)g->n_patch * Q);
+  // the folded solve contracts over a quarter patch: its own sizes name it
+  const bool fold = !lp && g->fold.ready;
+  const long cells = fold ? g->fold.hq : g->nang;
+  const std::string ka = tune_key(precision, 0, M, Q, cells), ks = tune_key(precision, 1, M, cells, (long)g->n_patch * Q);
   int best_va = *cur_va, best_sp = *cur_sp, best_vs = *cur_vs;
   // a plan in the separable form tunes that form's phases only (FP64): the
   // dense contractions keep their configuration
@@ -2093,6 +2292,7 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
                                  M * L.ldu, s);
   }
   auto ana = [&](int v, int sp) -> hipError_t {
+    if (fold) return fold_analysis(g, v, sp, tmp_part, s);
     if (!lp)
       return yyg::launch_gemm_nt_f64(v, 0, (int)M, Q, (int)g->nang, rho, g->nang, g->d_Bt, g->ldb, tmp_part, Q, sp,
                                      M * Q, s);
@@ -2102,6 +2302,7 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
                                   M * Q, s);
   };
   auto syn = [&](int v) -> hipError_t {
+    if (fold) return fold_synthesis(g, v, s);
     if (!lp)
       return yyg::launch_gemm_nt_f64(v, 1, (int)M, (int)g->nang, g->n_patch * Q, g->d_U, g->ldy, g->d_Y, g->ldy, tmp_out,
                                      g->nang, 1, 0, s);
@@ -2116,10 +2317,11 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
       int bm, bn;
       tile(v, &bm, &bn);
       long tiles = ((M + bm - 1) / bm) * ((Q + bn - 1) / bn);
-      int base = yyg::choose_split(tiles, g->nang);
+      if (fold) tiles = fold_analysis_tiles(g, bm, bn);
+      int base = yyg::choose_split(tiles, cells);
       int cands[] = {1, 2, 4, 8, 16, 32, base};
       for (int sp : cands) {
-        if (sp > smax || (long)sp * 64 > g->nang + 64) continue;
+        if (sp > smax || (long)sp * 64 > cells + 64) continue;
         double t = time_launch([&] { return ana(v, sp); }, s, 3);
         // the scan reads every partial once more: charge it at HBM speed
         t += (double)sp * M * Q * 8.0 / 5.0e9;
@@ -2487,6 +2689,7 @@ int yyg_batch_solve(yyg_batch *b, const double *const *d_rho, double *const *d_p
   hipStream_t s = stream ? as_stream(stream) : b->stream;
   for (int f = 0; f < n; ++f)
     if (int st = check_rho(b->grids[f], d_rho[f], s); st != YYG_OK) return st;
+  for (int f = 0; f < n; ++f) b->grids[f]->ahat_fold = false;
   for (int f = 0; f < n; ++f) b->grids[f]->ahat_cols = b->sep;  // the moments' layout the batch leaves
   bool changed = false;
   for (int f = 0; f < n; ++f)

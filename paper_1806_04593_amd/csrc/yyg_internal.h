@@ -237,6 +237,24 @@ void gemm_f64_variant_tile(int variant, int *bm, int *bn);
 hipError_t launch_gemm_nt_f64(int variant, int role, int M, int N, int K, const double *A, long lda, const double *B,
                               long ldb, double *C, long ldc, int nsplit, long c_split_stride, hipStream_t s);
 
+// Four contractions of one kind in one launch (the dense solve's parity
+// classes), tile shape `variant`: each as launch_gemm_nt_f64 with its own
+// sizes; nsplit and c_split_stride as there, C the first split's.
+struct GemmF64Quad {
+  GemmF64Args g[4];
+  int first[5];  // tile ranges (filled by the launcher)
+};
+hipError_t launch_gemm_f64_quad(int variant, int role, const GemmF64Quad &q, int nsplit, hipStream_t s);
+
+// Folds of the dense solve about the equator and the central meridian
+// (yyg_dense_fold.hip); rows <= 65535.
+hipError_t launch_fold_rows(const double *rho, double *F, int rows, int nt, int np, hipStream_t s);
+hipError_t launch_unfold_rows(const double *E, double *phi, int rows, int nt, int np, hipStream_t s);
+hipError_t launch_fold_analysis_basis(const double *Bt, long ldb, const int *cols, int n, int c, int nt, int np,
+                                      double *out, long ldo, int *flag, hipStream_t s);
+hipError_t launch_fold_synthesis_basis(const double *Y, long ldy, const int *ycols, int n, int c, int nt, int np,
+                                       double *out, long ldo, int *flag, hipStream_t s);
+
 // Persistent grouped FP64 GEMM: n_blocks blocks walk `items` = (problem,
 // tm, tn, split) over the problems' tiles of the variant's shape.  role 0/1
 // = analysis / synthesis with the plain epilogue, 2/3 with the general one
@@ -257,6 +275,7 @@ struct ScanArgs {
   double *U;
   long ldu;
   int cross;  // also write each row into the other patch's cross columns [Q, 2Q)
+  const int2 *ucol = nullptr;  // where column q goes in U: own, cross (null: q, Q + q)
 };
 
 // Grouped scan over several plans (each n_r <= 1024): items = (problem,
@@ -269,7 +288,7 @@ hipError_t launch_radial_scan_grouped(const ScanArgs *probs, const int4 *items, 
 // Ahat may be null (no copy of the reduced moments; nsplit must be 1).
 hipError_t launch_radial_scan(const double *part, int nsplit, long split_stride, double *Ahat, const double *coef,
                               const int *qdeg, int nR, int Q, int L, double negG, double *U, long ldu, int patches,
-                              hipStream_t s);
+                              hipStream_t s, const int2 *ucol = nullptr);
 
 hipError_t launch_expand_analysis_basis(const double *w, const double *Tt, const double *CS, int n_t, int n_p,
                                         int Q, double *Bt, long ldb, hipStream_t s);

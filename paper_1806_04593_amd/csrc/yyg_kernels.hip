@@ -36,7 +36,7 @@ namespace yyg {
 __global__ __launch_bounds__(1024) void radial_scan_loop_kernel(
     const double *__restrict__ part, int nsplit, long split_stride, double *__restrict__ Ahat,
     const double *__restrict__ coef, const int *__restrict__ qdeg, int nR, int Q, int L, double negG,
-    double *__restrict__ U, long ldu, int cross) {
+    double *__restrict__ U, long ldu, int cross, const int2 *__restrict__ ucol) {
   __shared__ double sI[16][64], sPa[16][64], sO[16][64], sPg[16][64];
   const int lane = threadIdx.x, w = threadIdx.y, nw = blockDim.y;
   const int q = blockIdx.x * 64 + lane;
@@ -44,6 +44,7 @@ __global__ __launch_bounds__(1024) void radial_scan_loop_kernel(
   const bool ok = q < Q;
   const int qq = ok ? q : 0;
   const int l = ok ? qdeg[q] : 0;
+  const int2 uc = ucol ? ucol[qq] : int2{qq, Q + qq};
   const int chunk = (nR + nw - 1) / nw;
   const int n0 = min(nR, w * chunk), n1 = min(nR, n0 + chunk);
   const long rbase = (long)p * nR;
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(1024) void radial_scan_loop_kernel(
   for (int n = n0; n < n1; ++n) {
     const double *c = cf + n * cstride;
     I = c[0] * I + c[1] * Ared[(rbase + n) * Q + q];
-    U[(rbase + n) * ldu + q] = I;
+    U[(rbase + n) * ldu + uc.x] = I;
   }
   O = Oin;
 #pragma unroll 4
@@ -101,9 +102,9 @@ __global__ __launch_bounds__(1024) void radial_scan_loop_kernel(
     const double *c = cf + n * cstride;
     const double an = (n + 1 < nR) ? Ared[(rbase + n + 1) * Q + q] : 0.0;
     O = c[2] * O + c[3] * an;
-    const double v = negG * (U[(rbase + n) * ldu + q] + O);
-    U[(rbase + n) * ldu + q] = v;
-    if (cross) U[(rbar + n) * ldu + Q + q] = v;
+    const double v = negG * (U[(rbase + n) * ldu + uc.x] + O);
+    U[(rbase + n) * ldu + uc.x] = v;
+    if (cross) U[(rbar + n) * ldu + uc.y] = v;
   }
 }
 
@@ -131,6 +132,7 @@ __device__ __forceinline__ void radial_scan_block(const ScanArgs &sa, int colblo
   const bool ok = q < Q;
   const int qq = ok ? q : 0;
   const int l = qdeg[qq];
+  const int2 uc = sa.ucol ? sa.ucol[qq] : int2{qq, Q + qq};
   const int chunk = (nR + 63) / 64;
   const int n0 = min(nR, y * chunk), n1 = min(nR, n0 + chunk);
   const int len = n1 - n0;
@@ -241,8 +243,8 @@ __device__ __forceinline__ void radial_scan_block(const ScanArgs &sa, int colblo
       if (i < len) {
         O = c2[u] * O + c3[u] * a[i + 1];
         const double v = negG * (Iv[i] + O);
-        U[(rbase + n0 + i) * ldu + q] = v;
-        if (sa.cross) U[(rbar + n0 + i) * ldu + Q + q] = v;
+        U[(rbase + n0 + i) * ldu + uc.x] = v;
+        if (sa.cross) U[(rbar + n0 + i) * ldu + uc.y] = v;
       }
     }
   }
@@ -723,6 +725,29 @@ hipError_t launch_grouped_variant(int role, const GemmF64Args *probs, const int4
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WGM, int WGN>
+hipError_t launch_quad_variant(int role, const GemmF64Quad &a, int nsplit, hipStream_t s) {
+  GemmF64Quad q = a;
+  long total = 0;
+  for (int c = 0; c < 4; ++c) {
+    GemmF64Args &g = q.g[c];
+    g.tiles_m = std::max(1, (g.M + BM - 1) / BM);
+    const int kps = (g.K + nsplit - 1) / nsplit;
+    g.k_per_split = (kps + kBK - 1) / kBK * kBK;
+    q.first[c] = (int)total;
+    total += (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+    if (total > INT_MAX) return hipErrorInvalidValue;
+  }
+  q.first[4] = (int)total;
+  if (total == 0) return hipSuccess;
+  dim3 grid((unsigned)total, nsplit), block(64 * WGM * WGN);
+  if (role == 0)
+    hipLaunchKernelGGL((gemm_nt_f64_quad<0, BM, BN, WGM, WGN>), grid, block, 0, s, q);
+  else
+    hipLaunchKernelGGL((gemm_nt_f64_quad<1, BM, BN, WGM, WGN>), grid, block, 0, s, q);
+  return hipGetLastError();
+}
+
 // Strided batch (see gemm_nt_f64_batched): role 0 stores C column-major
 // (kGemmCTrans), role 1 reads A k-major (kGemmATrans), roles 2 and 3 the
 // same with kGemmFoldA / kGemmFoldC; + kRoleDeep: with kGemmDeep.
@@ -803,6 +828,7 @@ typedef hipError_t (*gemm_f64_fn)(int, int, int, int, const double *, long, cons
                                   long, hipStream_t);
 typedef hipError_t (*batch_f64_fn)(int, const GemmF64Args &, hipStream_t);
 typedef hipError_t (*sep_f64_fn)(int, bool, const SepPhaseArgs &, hipStream_t);
+typedef hipError_t (*quad_f64_fn)(int, const GemmF64Quad &, int, hipStream_t);
 
 typedef hipError_t (*grouped_f64_fn)(int, const GemmF64Args *, const int4 *, int, int, hipStream_t);
 
@@ -812,12 +838,14 @@ struct F64Variant {
   grouped_f64_fn grouped;
   batch_f64_fn batch;
   sep_f64_fn sep;
+  quad_f64_fn quad;
 };
 
 #define YYG_F64_VARIANT(BM, BN, WM, WN)                                                                   \
   {                                                                                                        \
     BM, BN, 64 * WM * WN, WM, WN, launch_gemm_variant<BM, BN, WM, WN>, launch_grouped_variant<BM, BN, WM, WN>, \
-        launch_batch_variant<BM, BN, WM, WN>, launch_sep_variant<BM, BN, WM, WN>                          \
+        launch_batch_variant<BM, BN, WM, WN>, launch_sep_variant<BM, BN, WM, WN>,                         \
+        launch_quad_variant<BM, BN, WM, WN>                                                                \
   }
 
 const F64Variant kF64Variants[] = {
@@ -840,6 +868,11 @@ int gemm_f64_variant_count() { return (int)(sizeof(kF64Variants) / sizeof(kF64Va
 void gemm_f64_variant_tile(int v, int *bm, int *bn) {
   *bm = kF64Variants[v].bm;
   *bn = kF64Variants[v].bn;
+}
+
+hipError_t launch_gemm_f64_quad(int variant, int role, const GemmF64Quad &q, int nsplit, hipStream_t s) {
+  if (variant < 0 || variant >= gemm_f64_variant_count() || nsplit < 1) return hipErrorInvalidValue;
+  return kF64Variants[variant].quad(role, q, nsplit, s);
 }
 
 hipError_t launch_gemm_f64_grouped(int variant, int role, const GemmF64Args *probs, const int4 *items, int n_items,
@@ -943,11 +976,11 @@ hipError_t launch_gemm_nt_f64(int variant, int role, int M, int N, int K, const 
 
 hipError_t launch_radial_scan(const double *part, int nsplit, long split_stride, double *Ahat, const double *coef,
                               const int *qdeg, int nR, int Q, int L, double negG, double *U, long ldu, int patches,
-                              hipStream_t s) {
+                              hipStream_t s, const int2 *ucol) {
   if (patches != 1 && patches != 2) return hipErrorInvalidValue;
   const int cross = patches == 2 ? 1 : 0;
   if (!Ahat && nsplit != 1) return hipErrorInvalidValue;
-  ScanArgs sa{part, nsplit, split_stride, Ahat, coef, qdeg, nR, Q, L, negG, U, ldu, cross};
+  ScanArgs sa{part, nsplit, split_stride, Ahat, coef, qdeg, nR, Q, L, negG, U, ldu, cross, ucol};
   if (nR <= 64 * 4) {
     hipLaunchKernelGGL(radial_scan_kernel<4>, dim3((Q + 15) / 16, patches), dim3(16, 64), 0, s, sa);
   } else if (nR <= 64 * 8) {
@@ -959,7 +992,7 @@ hipError_t launch_radial_scan(const double *part, int nsplit, long split_stride,
     while (nw > 1 && nR / nw < 8) nw >>= 1;
     dim3 block(64, nw), grid((Q + 63) / 64, patches);
     hipLaunchKernelGGL(radial_scan_loop_kernel, grid, block, 0, s, part, nsplit, split_stride, Ahat, coef, qdeg, nR,
-                       Q, L, negG, U, ldu, cross);
+                       Q, L, negG, U, ldu, cross, ucol);
   }
   return hipGetLastError();
 }

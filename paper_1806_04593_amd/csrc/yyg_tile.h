@@ -657,6 +657,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_f64_kernel(GemmF64Args
   gemm_f64_tile<BM, BN, WGM, WGN, MODE>(g, tile % g.tiles_m, tile / g.tiles_m, blockIdx.y);
 }
 
+// Four contractions in one launch, tiles numbered one after the other.
+template <int ROLE, int BM, int BN, int WGM, int WGN>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_f64_quad(GemmF64Quad q) {
+  const int t = xcd_tile(blockIdx.x, q.first[4]);
+  const int c = t < q.first[1] ? 0 : t < q.first[2] ? 1 : t < q.first[3] ? 2 : 3;
+  const GemmF64Args &g = q.g[c];
+  const int tile = t - q.first[c];
+  gemm_f64_tile<BM, BN, WGM, WGN, 0>(g, tile % g.tiles_m, tile / g.tiles_m, blockIdx.y);
+}
+
 // Strided batch of equal-shape problems, one block per (problem, tile),
 // problem-major after the XCD remapping.
 template <int ROLE, int BM, int BN, int WGM, int WGN, int MODE>
