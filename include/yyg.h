@@ -450,7 +450,9 @@ int yyg_batch_autotune(yyg_batch *b, void *stream);
  * analysis work items, synthesis work items; for a separable batch the
  * variants and items are those of the phi analysis and phi synthesis, and
  * info[6..8] the tiles of the theta analysis, rotation and theta synthesis
- * (-1 for a dense batch).  Writes the first n entries (n <= 9). */
+ * (-1 for a dense batch).  Tiles are numbered from 0; 5 is the sweeps of the
+ * single-plan kernels over all fields (the default where every plan's degree
+ * and grid are within their reach).  Writes the first n entries (n <= 9). */
 int yyg_batch_info(const yyg_batch *b, int *info, int n);
 
 /* Solve every field: d_rho[f] / d_phi[f] are device arrays of field f in

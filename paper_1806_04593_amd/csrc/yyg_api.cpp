@@ -1255,15 +1255,24 @@ struct yyg_batch {
   // separable batches (FP64, every plan in the separable form): the five
   // phases and the column scans as grouped launches over all plans
   bool sep = false, sep_fold = false;
-  yyg::GemmF64Args *h_phi[2] = {nullptr, nullptr}, *d_phi[2] = {nullptr, nullptr};  // phi analysis / synthesis
+  // one pinned array and its device mirror hold the phi phases' arguments of
+  // the tiles and of the sweeps (analysis / synthesis)
+  char *h_args = nullptr, *d_args = nullptr;
+  size_t args_bytes = 0;
+  yyg::GemmF64Args *h_phi[2] = {nullptr, nullptr}, *d_phi[2] = {nullptr, nullptr};
+  yyg::PhiQuadArgs *h_quad[2] = {nullptr, nullptr}, *d_quad[2] = {nullptr, nullptr};
+  yyg::ThetaArgs *d_theta = nullptr;
   yyg::SepPhaseArgs *d_sargs = nullptr;
   yyg::ScanQArgs *d_qscan = nullptr;
   int2 *d_qitems = nullptr;
   int n_qitems = 0, max_nr = 0;
+  bool scan_two = false;
   int4 *d_sitems[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   int n_sitems[5] = {0, 0, 0, 0, 0};
   int svar[5] = {0, 0, 0, 0, 0};    // tile of each phase (yyg::sep_batch_tile)
   int sblocks[5] = {0, 0, 0, 0, 0};
+  int smax[5] = {0, 0, 0, 0, 0};    // sweeps: the largest shape or degree
+  size_t slds[5] = {0, 0, 0, 0, 0};
 };
 
 namespace {
@@ -1287,10 +1296,9 @@ void batch_free(yyg_batch *b) {
   }
   if (b->d_scan) (void)dev_free(b->d_scan);
   if (b->d_scan_items) (void)dev_free(b->d_scan_items);
-  for (int r = 0; r < 2; ++r) {
-    if (b->h_phi[r]) (void)hipHostFree(b->h_phi[r]);
-    if (b->d_phi[r]) (void)dev_free(b->d_phi[r]);
-  }
+  if (b->h_args) (void)hipHostFree(b->h_args);
+  if (b->d_args) (void)dev_free(b->d_args);
+  if (b->d_theta) (void)dev_free(b->d_theta);
   for (int r = 0; r < 5; ++r)
     if (b->d_sitems[r]) (void)dev_free(b->d_sitems[r]);
   if (b->d_sargs) (void)dev_free(b->d_sargs);
@@ -1384,6 +1392,8 @@ void batch_patch_pointers(yyg_batch *b) {
     if (b->sep) {
       b->h_phi[0][f].A = b->rho[f];
       b->h_phi[1][f].C = b->phi[f];
+      b->h_quad[0][f].X = b->rho[f];
+      b->h_quad[1][f].C = b->phi[f];
     } else if (b->precision == YYG_FP64) {
       b->h_f64[0][f].A = b->rho[f];
       b->h_f64[1][f].C = b->phi[f];
@@ -1512,7 +1522,75 @@ int batch_build(yyg_batch *b) {
 // longest contractions first so that the persistent blocks finish together:
 // (plan, tile row, tile column, z), z the strided-batch index (phi phases)
 // or the problem of the phase (theta phases, rotation).
+// The number past the tiles: the sweeps of yyg_phi_quad.hip and
+// yyg_theta.hip, where every plan can run them.
+bool sep_batch_sweeps(const yyg_batch *b, int r) {
+  for (int f = 0; f < (int)b->grids.size(); ++f) {
+    const yyg_grid *g = b->grids[f];
+    if (r == 0 || r == 4) {
+      if (!b->sep_fold || !yyg::phi_group_fits(r == 0, b->h_quad[r == 0 ? 0 : 1][f])) return false;
+    } else if ((r != 2 || g->n_patch == 2) && !g->sep.stream[r]) {
+      return false;
+    }
+  }
+  return true;
+}
+
+bool sep_batch_available(const yyg_batch *b, int r, int t) {
+  return t < yyg::sep_batch_tile_count() || (t == yyg::sep_batch_tile_count() && sep_batch_sweeps(b, r));
+}
+
+// Work items of the sweeps, one a block, the longest first; a plan's phi
+// blocks in runs per XCD (blocks go to the XCDs round-robin).  Theta blocks
+// take 16 row tiles (their basis is staged once for them), rotation blocks
+// 16 of a patch's.
+int sep_batch_sweep_items(yyg_batch *b, int r) {
+  std::vector<std::pair<long, int4>> work;
+  const int n = (int)b->grids.size();
+  b->smax[r] = 0;
+  b->slds[r] = 0;
+  for (int f = 0; f < n; ++f) {
+    const yyg_grid *g = b->grids[f];
+    const yyg::ThetaArgs &a = g->sep.theta;
+    if (r == 0 || r == 4) {
+      const yyg::PhiQuadArgs &q = b->h_quad[r == 0 ? 0 : 1][f];
+      const int blocks = yyg::phi_group_blocks(r == 0, q), shape = yyg::phi_group_shape(r == 0, q);
+      b->smax[r] = std::max(b->smax[r], shape);
+      const int per = blocks / 8, rem = blocks % 8;
+      for (int i = 0; i < blocks; ++i)
+        work.push_back({(long)q.S * shape, int4{f, (i & 7) * per + std::min(i & 7, rem) + (i >> 3), shape, 0}});
+      continue;
+    }
+    b->smax[r] = std::max(b->smax[r], g->L);
+    if (r == 2) {
+      if (g->n_patch != 2) continue;
+      b->slds[r] = std::max(b->slds[r], 2 * yyg::rotation_doubles(g->L) * sizeof(double));
+      const int tiles = (a.nR + 15) / 16, runs = (tiles + 15) / 16;
+      for (int l = 0; l <= g->L; ++l)
+        for (int u = 0; u < 3; ++u)
+          for (int i = 0; i < runs; ++i)
+            work.push_back({(long)(u == 0 ? 2 : 1) * l * (tiles / runs), int4{f, 3 * l + u, i, runs}});
+    } else {
+      const size_t lds = (r == 1 ? yyg::theta_ana_doubles(g->L, a.h) : yyg::theta_syn_doubles(g->L, a.h)) * sizeof(double);
+      b->slds[r] = std::max(b->slds[r], lds);
+      const int tiles = (a.Mr + 15) / 16, chunks = (tiles + 15) / 16;
+      for (int mc = 0; mc < 2 * g->L + 1; ++mc)
+        for (int i = 0; i < chunks; ++i)
+          work.push_back({(long)a.h * (g->L + 2 - (mc + 1) / 2) * (tiles / chunks), int4{f, mc, i, chunks}});
+    }
+  }
+  std::stable_sort(work.begin(), work.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+  std::vector<int4> items(work.size());
+  for (size_t i = 0; i < work.size(); ++i) items[i] = work[i].second;
+  const int st = upload(&b->d_sitems[r], items);
+  if (st != YYG_OK) return st;
+  b->n_sitems[r] = (int)items.size();
+  b->svar[r] = yyg::sep_batch_tile_count();
+  return YYG_OK;
+}
+
 int sep_batch_set_items(yyg_batch *b, int r, int t) {
+  if (t == yyg::sep_batch_tile_count()) return sep_batch_sweep_items(b, r);
   int bm, bn, threads;
   yyg::sep_batch_tile(t, &bm, &bn, &threads);
   std::vector<std::pair<long, int4>> work;
@@ -1567,13 +1645,21 @@ int sep_batch_build(yyg_batch *b) {
   // mode for all plans)
   b->sep_fold = true;
   for (int f = 0; f < n; ++f) b->sep_fold = b->sep_fold && b->grids[f]->sep.fold;
-  for (int r = 0; r < 2; ++r)
-    if (hipHostMalloc(reinterpret_cast<void **>(&b->h_phi[r]), n * sizeof(yyg::GemmF64Args), 0) != hipSuccess ||
-        dev_malloc(reinterpret_cast<void **>(&b->d_phi[r]), n * sizeof(yyg::GemmF64Args)) != hipSuccess) {
-      (void)hipGetLastError();
-      return YYG_ERR_OUT_OF_MEMORY;
-    }
+  const size_t pb = n * sizeof(yyg::GemmF64Args), qb = n * sizeof(yyg::PhiQuadArgs);
+  b->args_bytes = 2 * (pb + qb);
+  if (hipHostMalloc(reinterpret_cast<void **>(&b->h_args), b->args_bytes, 0) != hipSuccess ||
+      dev_malloc(reinterpret_cast<void **>(&b->d_args), b->args_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return YYG_ERR_OUT_OF_MEMORY;
+  }
+  for (int r = 0; r < 2; ++r) {
+    b->h_phi[r] = reinterpret_cast<yyg::GemmF64Args *>(b->h_args + r * pb);
+    b->d_phi[r] = reinterpret_cast<yyg::GemmF64Args *>(b->d_args + r * pb);
+    b->h_quad[r] = reinterpret_cast<yyg::PhiQuadArgs *>(b->h_args + 2 * pb + r * qb);
+    b->d_quad[r] = reinterpret_cast<yyg::PhiQuadArgs *>(b->d_args + 2 * pb + r * qb);
+  }
   std::vector<yyg::SepPhaseArgs> sargs(n);
+  std::vector<yyg::ThetaArgs> theta(n);
   std::vector<yyg::ScanQArgs> qscan(n);
   std::vector<int2> qitems;
   for (int f = 0; f < n; ++f) {
@@ -1581,38 +1667,53 @@ int sep_batch_build(yyg_batch *b) {
     auto &S = g->sep;
     b->h_phi[0][f] = b->sep_fold ? S.phi_ana_f : S.phi_ana;
     b->h_phi[1][f] = b->sep_fold ? S.phi_syn_f : S.phi_syn;
+    b->h_quad[0][f] = S.quad_ana;
+    b->h_quad[1][f] = S.quad_syn;
+    theta[f] = S.theta;
     sargs[f] = S.args;
     const int chunk = ((g->n_r + 63) / 64) | 1;
     qscan[f] = yyg::ScanQArgs{g->n_patch == 2 ? S.At : g->d_Ahat, S.coefS, g->d_qdeg, g->n_r, g->L, chunk,
                               g->n_patch, -g->G, S.Ut};
     b->max_nr = std::max(b->max_nr, g->n_r);
-    for (int q = 0; q < g->Q; ++q) qitems.push_back(int2{f, q});
   }
+  // the longest columns first, two per block where several such blocks fit a CU
+  b->scan_two = yyg::radial_scan_q_two(b->max_nr);
+  std::vector<int> order(n);
+  for (int f = 0; f < n; ++f) order[f] = f;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->grids[x]->n_r > b->grids[y]->n_r; });
+  for (int f : order)
+    for (int l = 0; l <= b->grids[f]->L; ++l)
+      for (int k = 0; k < 2 * l + 1; k += b->scan_two ? 2 : 1) qitems.push_back(int2{f, l * l + k});
   int st = upload(&b->d_sargs, sargs);
+  if (st == YYG_OK) st = upload(&b->d_theta, theta);
   if (st == YYG_OK) st = upload(&b->d_qscan, qscan);
   if (st == YYG_OK) st = upload(&b->d_qitems, qitems);
   b->n_qitems = (int)qitems.size();
-  // default tiles: 64 x 80 for the phi analysis, 128 x 48 for the phi
+  // the sweeps where every plan can run them; else tiles: 64 x 80 for the phi analysis, 128 x 48 for the phi
   // synthesis, 32 x 32 for the theta phases and the rotation
   const int def[5] = {3, 0, 0, 0, 4};
-  for (int r = 0; r < 5 && st == YYG_OK; ++r) st = sep_batch_set_items(b, r, def[r]);
+  for (int r = 0; r < 5 && st == YYG_OK; ++r)
+    st = sep_batch_set_items(b, r, sep_batch_sweeps(b, r) ? yyg::sep_batch_tile_count() : def[r]);
   return st;
 }
 
 // The batched separable solve on s; with ev (6 events) recorded before
 // the argument copies and after each of the six launches.
 hipError_t sep_batch_enqueue(yyg_batch *b, hipStream_t s, hipEvent_t *ev) {
-  const int n = (int)b->grids.size();
   hipError_t e = hipSuccess;
   auto mark = [&](int i) {
     if (ev && e == hipSuccess) e = hipEventRecord(ev[i], s);
   };
   mark(0);
-  e = hipMemcpyAsync(b->d_phi[0], b->h_phi[0], n * sizeof(yyg::GemmF64Args), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b->d_phi[1], b->h_phi[1], n * sizeof(yyg::GemmF64Args), hipMemcpyHostToDevice, s);
+  e = hipMemcpyAsync(b->d_args, b->h_args, b->args_bytes, hipMemcpyHostToDevice, s);
   auto phase = [&](int r) {
-    if (e == hipSuccess)
+    if (e != hipSuccess) return;
+    const bool sweep = b->svar[r] == yyg::sep_batch_tile_count();
+    if (sweep && (r == 0 || r == 4))
+      e = yyg::launch_phi_group(r == 0, b->smax[r], b->d_quad[r == 0 ? 0 : 1], b->d_sitems[r], b->n_sitems[r], s);
+    else if (sweep)
+      e = yyg::launch_theta_group(r, b->smax[r], b->slds[r], b->d_theta, b->d_sitems[r], b->n_sitems[r], s);
+    else
       e = yyg::launch_sep_batch_phase(b->svar[r], r, b->sep_fold, b->d_phi[r == 0 ? 0 : 1], b->d_sargs, b->d_sitems[r],
                                       b->n_sitems[r], b->sblocks[r], s);
   };
@@ -1622,8 +1723,7 @@ hipError_t sep_batch_enqueue(yyg_batch *b, hipStream_t s, hipEvent_t *ev) {
   phase(2);
   mark(2);
   if (e == hipSuccess)
-    e = yyg::launch_radial_scan_q_grouped(b->d_qscan, b->d_qitems, b->n_qitems, std::min(b->n_qitems, b->cus * 4),
-                                          b->max_nr, s);
+    e = yyg::launch_radial_scan_q_grouped(b->d_qscan, b->d_qitems, b->n_qitems, b->scan_two, b->max_nr, s);
   mark(3);
   phase(3);
   mark(4);
@@ -2618,7 +2718,8 @@ int yyg_batch_autotune(yyg_batch *b, void *stream) {
       if (r == 2 && b->n_sitems[2] == 0) continue;  // no two-patch plan: nothing to rotate
       int best = b->svar[r];
       double bt = 1e30;
-      for (int t = 0; t < yyg::sep_batch_tile_count(); ++t) {
+      for (int t = 0; t <= yyg::sep_batch_tile_count(); ++t) {
+        if (!sep_batch_available(b, r, t)) continue;
         int st = sep_batch_set_items(b, r, t);
         if (st != YYG_OK) return st;
         const double tm = time_launch([&] { return sep_batch_enqueue(b, s, nullptr); }, s, 3);

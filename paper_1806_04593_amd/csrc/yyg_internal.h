@@ -158,6 +158,14 @@ int phi_quad_steps(int L);   // synthesis steps of four columns per group
 int phi_quad_variant_count();
 int phi_quad_default(bool analysis, const PhiQuadArgs &a, int cus);  // the variant of a plan not tuned
 hipError_t launch_phi_quad(int v, bool analysis, const PhiQuadArgs &a, int cus, hipStream_t s);
+// Several plans' sweeps in one launch: whether a plan's sizes are within its
+// reach, its blocks, its shape (the largest of the batch picks the kernel),
+// and the launch over items (plan, block, shape, -).
+bool phi_group_fits(bool analysis, const PhiQuadArgs &a);
+int phi_group_blocks(bool analysis, const PhiQuadArgs &a);
+int phi_group_shape(bool analysis, const PhiQuadArgs &a);
+hipError_t launch_phi_group(bool analysis, int max_shape, const PhiQuadArgs *args, const int4 *items, int n_items,
+                            hipStream_t s);
 int phi_quad_kernel_name(int v, bool analysis, const PhiQuadArgs &a, char *buf, size_t n);
 
 // Folded phi synthesis with every wave loading its MFMA fragments straight
@@ -213,6 +221,11 @@ size_t theta_syn_doubles(int L, int h);  // sts
 size_t rotation_doubles(int L);          // std
 bool theta_stream_fits(int phase, int L, int h);
 hipError_t launch_theta_stream(int phase, int variant, const ThetaArgs &a, int cus, hipStream_t s);
+// The same over several plans (degrees at most L, lds bytes the largest
+// plan's): items (plan, column, chunk, chunks) of phases 1 and 3, (plan,
+// 3 degree + class unit, run, runs) of phase 2.
+hipError_t launch_theta_group(int phase, int L, size_t lds, const ThetaArgs *args, const int4 *items, int n_items,
+                              hipStream_t s);
 int theta_stream_kernel_name(int phase, int variant, const ThetaArgs &a, char *buf, size_t n);
 
 // phase 1 theta analysis, 2 rotation (two patches), 3 theta synthesis;
@@ -372,10 +385,12 @@ struct ScanQArgs {
   double negG;
   double *Ut;
 };
-// items = (plan, column q); blocks of 128 threads with the LDS of the
-// largest plan (max_nR shells).
-hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items, int n_items, int n_blocks,
-                                        int max_nR, hipStream_t s);
+// items = (plan, column q), one a block, with the LDS of the largest plan
+// (max_nR shells); two = two neighbouring columns of a degree per block, q and
+// q + 1 (an item's q is even within its degree).
+bool radial_scan_q_two(int max_nR);
+hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items, int n_items, bool two, int max_nR,
+                                        hipStream_t s);
 // Grouped separable phases over several plans with one of
 // sep_batch_tile_count() tile shapes: phase 0 / 4 the phi transforms
 // (folded or not; items (plan, tile row, tile column, batch index z) over

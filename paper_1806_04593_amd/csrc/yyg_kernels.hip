@@ -523,7 +523,8 @@ __device__ __forceinline__ void radial_scan_q_body(const double *__restrict__ X,
                                                    double *smem, int q2 = -1) {
   const int l = qdeg[q];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int col = NCOL > 1 ? w / P : 0, p = NCOL > 1 ? w - col * P : w;
+  // (waves past NCOL P: a block sized for two patches with a plan of one)
+  const int col = NCOL > 1 ? min(w / P, NCOL - 1) : 0, p = NCOL > 1 ? w - col * P : w;
   const bool active = p < P && (col == 0 || q2 >= 0);
   const int pa = p < P ? p : 0;                       // an inactive wave addresses patch 0 and stores nothing
   if (col == 1 && q2 >= 0) q = q2;
@@ -653,18 +654,20 @@ __global__ __launch_bounds__(256) void radial_scan_q2_kernel(const double *__res
   radial_scan_q_body<CMAX, 2>(X, coefS, qdeg, nR, L, chunk, negG, Ut, q, P, smem, j < l ? q + 1 : -1);
 }
 
-// The same over the columns of several plans (batched separable solves):
-// blocks of two waves walk work items (plan, column q).
-template <int CMAX>
-__global__ __launch_bounds__(128) void radial_scan_q_grouped(const ScanQArgs *__restrict__ args,
-                                                             const int2 *__restrict__ items, int n_items) {
+// The same over the columns of several plans (batched separable solves): a
+// block takes work item (plan, column q), NCOL columns from q on (the second
+// absent at a degree's last).  24 plans of 100 to 600 shells, lmax 10 to 30
+// (118 MB, 24 us at the copy's rate): one column per block and walking blocks
+// 75 to 83 us, two columns and an item a block 59.
+template <int CMAX, int NCOL>
+__global__ __launch_bounds__(128 * NCOL) void radial_scan_q_grouped(const ScanQArgs *__restrict__ args,
+                                                                    const int2 *__restrict__ items) {
   extern __shared__ double smem[];
-  for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
-    const int2 it = items[w];
-    const ScanQArgs a = args[it.x];
-    __syncthreads();  // the previous item's LDS reads are done
-    radial_scan_q_body<CMAX>(a.X, a.coefS, a.qdeg, a.nR, a.L, a.chunk, a.negG, a.Ut, it.y, a.P, smem);
-  }
+  const int2 it = items[blockIdx.x];
+  const ScanQArgs a = args[it.x];
+  const int l = a.qdeg[it.y];
+  radial_scan_q_body<CMAX, NCOL>(a.X, a.coefS, a.qdeg, a.nR, a.L, a.chunk, a.negG, a.Ut, it.y, a.P, smem,
+                                 NCOL > 1 && it.y + 1 < (l + 1) * (l + 1) ? it.y + 1 : -1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1085,10 +1088,14 @@ hipError_t launch_radial_scan_q(const double *X, const double *coefS, const int 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items, int n_items, int n_blocks,
-                                        int max_nR, hipStream_t s) {
+// Three blocks of two columns and more fit a CU (up to 852 shells), and a
+// lane's chunk its instances.
+bool radial_scan_q_two(int max_nR) { return radial_scan_q2_lds(max_nR, 2) <= kScanQMaxLds / 3; }
+
+hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items, int n_items, bool two, int max_nR,
+                                        hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  const size_t lds = radial_scan_q_lds(max_nR, 2);
+  const size_t lds = two ? radial_scan_q2_lds(max_nR, 2) : radial_scan_q_lds(max_nR, 2);
   if (lds > kScanQMaxLds) return hipErrorInvalidValue;
   const int chunk = ((max_nR + 63) / 64) | 1;
   auto go = [&](auto kern) {
@@ -1096,13 +1103,19 @@ hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items
         hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
       return hipGetLastError();
-    hipLaunchKernelGGL(kern, dim3(n_blocks), dim3(128), lds, s, args, items, n_items);
+    hipLaunchKernelGGL(kern, dim3(n_items), dim3(two ? 256 : 128), lds, s, args, items);
     return hipGetLastError();
   };
-  if (chunk <= 7) return go(radial_scan_q_grouped<7>);
-  if (chunk <= 15) return go(radial_scan_q_grouped<15>);
-  if (chunk <= 31) return go(radial_scan_q_grouped<31>);
-  if (chunk <= 63) return go(radial_scan_q_grouped<63>);
+  if (two) {
+    if (chunk <= 7) return go(radial_scan_q_grouped<7, 2>);
+    if (chunk <= 11) return go(radial_scan_q_grouped<11, 2>);
+    if (chunk <= 15) return go(radial_scan_q_grouped<15, 2>);
+  }
+  if (two) return hipErrorInvalidValue;
+  if (chunk <= 7) return go(radial_scan_q_grouped<7, 1>);
+  if (chunk <= 15) return go(radial_scan_q_grouped<15, 1>);
+  if (chunk <= 31) return go(radial_scan_q_grouped<31, 1>);
+  if (chunk <= 63) return go(radial_scan_q_grouped<63, 1>);
   return hipErrorInvalidValue;
 }
 

@@ -54,6 +54,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const double *p, lon
 __device__ __forceinline__ int quad_order(int gr, int o) { return 2 * o + (gr == 0 ? 0 : gr == 2 ? 2 : 1); }
 __device__ __forceinline__ int quad_column(int gr, int m) { return gr < 2 ? max(2 * m - 1, 0) : 2 * m; }
 
+constexpr int kAnaLdp = 18;  // a folded row of 16 points in LDS
+
 // Analysis sweep, one row tile per wave: 16 (patch, shell) rows of one
 // colatitude, every azimuthal column, so that a density value is read once.
 // A stage is 16 folded points.  Its density loads cover 128 contiguous bytes
@@ -65,13 +67,12 @@ __device__ __forceinline__ int quad_column(int gr, int m) { return gr < 2 ? max(
 // through LDS in operand order, shared by the block's waves, double-buffered
 // with one barrier per stage.  Stages without partners (t >= T2) load and
 // fold two places only.
-// TJ tiles of 16 outputs per group; XC: the even cosines number 16 TJ + 1
+// `lds`: phi_ana_quad_lds doubles.  TJ tiles of 16 outputs per group; XC: the even cosines number 16 TJ + 1
 // and the last one is summed on the vector units.
 template <int TJ, bool XC, int NW, bool WGT>
-__device__ __forceinline__ void phi_ana_quad_tiles(const PhiQuadArgs &a, int blk) {
-  constexpr int NT = 64 * NW, CH = 4 * TJ * 256 + (XC ? 16 : 0), NB = (CH / 2 + NT - 1) / NT, LDP = 18;
-  __shared__ __attribute__((aligned(16))) double Bs[2][CH];
-  __shared__ __attribute__((aligned(16))) double Ps[NW][4][16 * LDP];
+__device__ __forceinline__ void phi_ana_quad_tiles(const PhiQuadArgs &a, int blk, double *lds) {
+  constexpr int NT = 64 * NW, CH = 4 * TJ * 256 + (XC ? 16 : 0), NB = (CH / 2 + NT - 1) / NT, LDP = kAnaLdp;
+  double *const Bs[2] = {lds, lds + CH};
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;   // operand layout
   const int lr = lane >> 3, lt = 2 * (lane & 7);  // load layout: rows lr and lr + 8, points lt and lt + 1
@@ -81,7 +82,7 @@ __device__ __forceinline__ void phi_ana_quad_tiles(const PhiQuadArgs &a, int blk
   const double *__restrict__ px0 = a.X + (long)min(rt * 16 + lr, a.Mr - 1) * a.ld + (long)j * a.np;
   const double *__restrict__ px1 = a.X + (long)min(rt * 16 + lr + 8, a.Mr - 1) * a.ld + (long)j * a.np;
   const double *__restrict__ pw = a.W + (long)j * 2 * a.Kp + lt;
-  double *__restrict__ const ps = &Ps[wave][0][0];
+  double *__restrict__ const ps = lds + 2 * CH + wave * 64 * LDP;
 
   dbl4q acc[4][TJ];
 #pragma unroll
@@ -240,9 +241,39 @@ __device__ __forceinline__ void phi_ana_quad_tiles(const PhiQuadArgs &a, int blk
   }
 }
 
+constexpr int phi_ana_quad_lds(int TJ, bool XC, int NW) { return 2 * (4 * TJ * 256 + (XC ? 16 : 0)) + NW * 64 * kAnaLdp; }
+
 template <int TJ, bool XC, int NW, bool WGT>
 __global__ __launch_bounds__(64 * NW, TJ == 1 ? 3 : TJ < 4 ? 2 : 1) void phi_ana_quad(PhiQuadArgs a) {
-  phi_ana_quad_tiles<TJ, XC, NW, WGT>(a, quad_xcd(blockIdx.x, gridDim.x));
+  __shared__ __attribute__((aligned(16))) double lds[phi_ana_quad_lds(TJ, XC, NW)];
+  phi_ana_quad_tiles<TJ, XC, NW, WGT>(a, quad_xcd(blockIdx.x, gridDim.x), lds);
+}
+
+// The sweep over several plans of up to TM tiles of outputs per group: items
+// (plan, block of the plan, shape: 4 tiles + 2 extra output + 1 weights), one
+// a block.  Bound by the density's stream and its latency: 24 plans of 100 to
+// 600 shells at 2 to 4 degrees, lmax 10 to 30 (0.72 GB there and back, 145 us
+// at the copy's rate): tiles folded once 248 us, here 204 with two waves a
+// block, 197 with four; the form with the basis in registers, its blocks
+// shared out among the plans, 252.
+template <int TM, int NW>
+__global__ __launch_bounds__(64 * NW, TM == 1 ? 3 : 2) void phi_ana_group(const PhiQuadArgs *__restrict__ args,
+                                                                         const int4 *__restrict__ items) {
+  __shared__ __attribute__((aligned(16))) double lds[phi_ana_quad_lds(TM, true, NW)];
+  const int4 it = items[blockIdx.x];
+  const PhiQuadArgs a = args[it.x];
+  switch (it.z) {  // uniform
+    case 4: phi_ana_quad_tiles<1, false, NW, false>(a, it.y, lds); break;
+    case 5: phi_ana_quad_tiles<1, false, NW, true>(a, it.y, lds); break;
+    case 6: phi_ana_quad_tiles<1, true, NW, false>(a, it.y, lds); break;
+    case 7: phi_ana_quad_tiles<1, true, NW, true>(a, it.y, lds); break;
+  }
+  if constexpr (TM >= 2) switch (it.z) {
+      case 8: phi_ana_quad_tiles<2, false, NW, false>(a, it.y, lds); break;
+      case 9: phi_ana_quad_tiles<2, false, NW, true>(a, it.y, lds); break;
+      case 10: phi_ana_quad_tiles<2, true, NW, false>(a, it.y, lds); break;
+      case 11: phi_ana_quad_tiles<2, true, NW, true>(a, it.y, lds); break;
+    }
 }
 
 // Lane groups 2 and 3 of a trade places with groups 0 and 1 of b.
@@ -255,6 +286,8 @@ __device__ __forceinline__ void quad_swap(double &a, double &b) {
   b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
 }
 
+constexpr int phi_syn_quad_lds(int NQ) { return 8 * ((NQ + 1) / 2) * 128; }
+
 // Synthesis sweep, one row tile per wave: the tile's coefficients (every
 // azimuthal column of 16 rows of one colatitude) load once into registers
 // as A operands; the basis passes through LDS one tile of 16 folded cells
@@ -262,9 +295,9 @@ __device__ __forceinline__ void quad_swap(double &a, double &b) {
 // four sums give the four symmetric cells.
 // NQ steps of four columns per group (groups 1-3 may hold one fewer).
 template <int NQ, int NW, bool PAIR>
-__device__ __forceinline__ void phi_syn_quad_tiles(const PhiQuadArgs &a, int blk) {
-  constexpr int NT = 64 * NW, NP = (NQ + 1) / 2, CH = 4 * NP * 128, NB = (CH / 2 + NT - 1) / NT;
-  __shared__ __attribute__((aligned(16))) double Bs[2][CH];
+__device__ __forceinline__ void phi_syn_quad_tiles(const PhiQuadArgs &a, int blk, double *lds) {
+  constexpr int NT = 64 * NW, NP = (NQ + 1) / 2, CH = phi_syn_quad_lds(NQ) / 2, NB = (CH / 2 + NT - 1) / NT;
+  double *const Bs[2] = {lds, lds + CH};
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, r16 = lane & 15;
   const int total = a.nt * ((a.Mr + 15) / 16);
@@ -380,7 +413,34 @@ __device__ __forceinline__ void phi_syn_quad_tiles(const PhiQuadArgs &a, int blk
 
 template <int NQ, int NW, bool PAIR>
 __global__ __launch_bounds__(64 * NW, NQ <= 3 ? 3 : NQ <= 11 ? 2 : 1) void phi_syn_quad(PhiQuadArgs a) {
-  phi_syn_quad_tiles<NQ, NW, PAIR>(a, quad_xcd(blockIdx.x, gridDim.x));
+  __shared__ __attribute__((aligned(16))) double lds[phi_syn_quad_lds(NQ)];
+  phi_syn_quad_tiles<NQ, NW, PAIR>(a, quad_xcd(blockIdx.x, gridDim.x), lds);
+}
+
+// The sweep over several plans of up to NM steps: items (plan, block of the
+// plan, shape: 2 steps + 1 with partners), one a block.  The same batch: 239
+// us in tiles, 172 here.
+template <int NM, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void phi_syn_group(const PhiQuadArgs *__restrict__ args,
+                                                            const int4 *__restrict__ items) {
+  __shared__ __attribute__((aligned(16))) double lds[phi_syn_quad_lds(NM)];
+  const int4 it = items[blockIdx.x];
+  const PhiQuadArgs a = args[it.x];
+#define YYG_STEPS(NQ)                                                        \
+  case 2 * NQ: phi_syn_quad_tiles<NQ, NW, false>(a, it.y, lds); break;       \
+  case 2 * NQ + 1: phi_syn_quad_tiles<NQ, NW, true>(a, it.y, lds); break
+  switch (it.z) {  // uniform
+    YYG_STEPS(1);
+    YYG_STEPS(2);
+    YYG_STEPS(3);
+    YYG_STEPS(4);
+  }
+  if constexpr (NM >= 9) switch (it.z) {
+      YYG_STEPS(5);
+      YYG_STEPS(6);
+      YYG_STEPS(9);
+    }
+#undef YYG_STEPS
 }
 
 // Synthesis with the basis in registers: wave w of a block owns one tile of
@@ -994,6 +1054,41 @@ hipError_t launch_phi_quad(int v, bool analysis, const PhiQuadArgs &a, int cus, 
     case 8: return analysis ? launch_ana_w<8>(a, blocks, s) : launch_syn_w<8>(a, blocks, s);
     default: return analysis ? launch_ana_w<4>(a, blocks, s) : launch_syn_w<4>(a, blocks, s);
   }
+}
+
+// Waves of the batch's blocks: four, so that LDS leaves three waves per SIMD in
+// the analysis (two with a single plan's two waves a block).
+constexpr int kGroupAna = 4, kGroupSyn = 4;
+
+bool phi_group_fits(bool analysis, const PhiQuadArgs &a) {
+  const long tiles = (long)a.nt * ((a.Mr + 15) / 16);
+  return a.np >= 2 && a.S >= 1 && a.K > 0 && tiles < INT_MAX / 8 &&
+         (analysis ? phi_quad_tiles(a.L) <= 2 : phi_quad_steps(a.L) >= 1 && phi_quad_steps(a.L) <= 9);
+}
+
+int phi_group_blocks(bool analysis, const PhiQuadArgs &a) {
+  const int nw = analysis ? kGroupAna : kGroupSyn;
+  return (int)(((long)a.nt * ((a.Mr + 15) / 16) + nw - 1) / nw);
+}
+
+int phi_group_shape(bool analysis, const PhiQuadArgs &a) {
+  return analysis ? 4 * phi_quad_tiles(a.L) + 2 * (phi_quad_extra(a.L) ? 1 : 0) + (a.W ? 1 : 0)
+                  : 2 * phi_quad_steps(a.L) + (a.T2 > 0 ? 1 : 0);
+}
+
+hipError_t launch_phi_group(bool analysis, int max_shape, const PhiQuadArgs *args, const int4 *items, int n_items,
+                            hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid(n_items), block(64 * (analysis ? kGroupAna : kGroupSyn));
+  if (analysis && max_shape < 8)
+    hipLaunchKernelGGL((phi_ana_group<1, kGroupAna>), grid, block, 0, s, args, items);
+  else if (analysis)
+    hipLaunchKernelGGL((phi_ana_group<2, kGroupAna>), grid, block, 0, s, args, items);
+  else if (max_shape < 10)
+    hipLaunchKernelGGL((phi_syn_group<4, kGroupSyn>), grid, block, 0, s, args, items);
+  else
+    hipLaunchKernelGGL((phi_syn_group<9, kGroupSyn>), grid, block, 0, s, args, items);
+  return hipGetLastError();
 }
 
 int phi_quad_kernel_name(int v, bool analysis, const PhiQuadArgs &a, char *buf, size_t n) {

@@ -95,11 +95,11 @@ __device__ __forceinline__ void theta_ana_sweep(const ThetaArgs &a, const double
   }
 }
 
-// NW waves per block, TM the most 16-degree tiles a parity holds (m = 0).
+// One block: the row tiles of `chunk` (of `chunks`) of column mc.  NW waves,
+// TM the most 16-degree tiles a parity holds (m = 0).
 template <int TM, int NW>
-__global__ __launch_bounds__(64 * NW) void theta_ana_stream(ThetaArgs a, int chunks) {
-  extern __shared__ __attribute__((aligned(16))) double Bs[];
-  const int mc = blockIdx.x / chunks, chunk = blockIdx.x - mc * chunks, m = (mc + 1) >> 1;
+__device__ __forceinline__ void theta_ana_block(const ThetaArgs &a, double *Bs, int mc, int chunk, int chunks) {
+  const int m = (mc + 1) >> 1;
   const int ng = (a.h + 15) / 16, T = ((a.L - m) / 2 + 16) / 16;  // even degrees l = m, m + 2, ..: (L - m) / 2 + 1
   const dbl2t *__restrict__ src = reinterpret_cast<const dbl2t *>(a.TA + (long)m * a.sta);
   for (int e = threadIdx.x; e < ng * 4 * T * 64; e += 64 * NW) *reinterpret_cast<dbl2t *>(Bs + 2 * e) = src[e];
@@ -114,6 +114,26 @@ __global__ __launch_bounds__(64 * NW) void theta_ana_stream(ThetaArgs a, int chu
     theta_ana_sweep<(TM >= 3 ? 3 : 1)>(a, Bs, mc, m, ng, t_beg, t_end, NW);
 }
 
+template <int TM, int NW>
+__global__ __launch_bounds__(64 * NW) void theta_ana_stream(ThetaArgs a, int chunks) {
+  extern __shared__ __attribute__((aligned(16))) double Bs[];
+  const int mc = blockIdx.x / chunks;
+  theta_ana_block<TM, NW>(a, Bs, mc, blockIdx.x - mc * chunks, chunks);
+}
+
+// The same over the columns of several plans: items (plan, column, chunk,
+// chunks), one a block.  24 plans of 100 to 600 shells at 2 to 4 degrees, lmax
+// 10 to 30: analysis 65 us in tiles, 59 here; synthesis 78, 58; rotation 63,
+// 40.
+template <int TM, int NW>
+__global__ __launch_bounds__(64 * NW) void theta_ana_group(const ThetaArgs *__restrict__ args,
+                                                           const int4 *__restrict__ items) {
+  extern __shared__ __attribute__((aligned(16))) double Bs[];
+  const int4 it = items[blockIdx.x];
+  const ThetaArgs a = args[it.x];
+  theta_ana_block<TM, NW>(a, Bs, it.y, it.z, it.w);
+}
+
 // Synthesis of azimuthal column mc: V[mc][j][row] = sum_l P_l^m(t_j)
 // Ut[mc][l][row].  A block holds the column's folded basis in LDS; each wave
 // walks row tiles, a tile's coefficients (KQ steps of four degrees per
@@ -121,9 +141,8 @@ __global__ __launch_bounds__(64 * NW) void theta_ana_stream(ThetaArgs a, int chu
 // of each colatitude and of its mirror.  Same sizes as above: 171 us in
 // 64 x 32 tiles, 138 in the best tile, 105 here; 70 -> 49.
 template <int KQ, int NW>
-__global__ __launch_bounds__(64 * NW) void theta_syn_stream(ThetaArgs a, int chunks) {
-  extern __shared__ __attribute__((aligned(16))) double Bs[];
-  const int mc = blockIdx.x / chunks, chunk = blockIdx.x - mc * chunks, m = (mc + 1) >> 1;
+__device__ __forceinline__ void theta_syn_block(const ThetaArgs &a, double *Bs, int mc, int chunk, int chunks) {
+  const int m = (mc + 1) >> 1;
   const int kp = ((a.L - m) / 2 + 8) / 8;  // pairs of steps: ceil(((L - m) / 2 + 1) / 8)
   const int jt = (a.h + 15) / 16;
   const dbl2t *__restrict__ src = reinterpret_cast<const dbl2t *>(a.TS + (long)m * a.sts);
@@ -184,6 +203,22 @@ __global__ __launch_bounds__(64 * NW) void theta_syn_stream(ThetaArgs a, int chu
   }
 }
 
+template <int KQ, int NW>
+__global__ __launch_bounds__(64 * NW) void theta_syn_stream(ThetaArgs a, int chunks) {
+  extern __shared__ __attribute__((aligned(16))) double Bs[];
+  const int mc = blockIdx.x / chunks;
+  theta_syn_block<KQ, NW>(a, Bs, mc, blockIdx.x - mc * chunks, chunks);
+}
+
+template <int KQ, int NW>
+__global__ __launch_bounds__(64 * NW) void theta_syn_group(const ThetaArgs *__restrict__ args,
+                                                           const int4 *__restrict__ items) {
+  extern __shared__ __attribute__((aligned(16))) double Bs[];
+  const int4 it = items[blockIdx.x];
+  const ThetaArgs a = args[it.x];
+  theta_syn_block<KQ, NW>(a, Bs, it.y, it.z, it.w);
+}
+
 // column (within its degree) of member i of class c: 0 cos m = 2 i, 1 cos
 // m = 2 i + 1, 2 sin m = 2 i + 2, 3 sin m = 2 i + 1
 __device__ __forceinline__ int class_column(int c, int i) {
@@ -209,12 +244,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t theta_buffer(const double *p, 
 // them twice): 1000 shells, lmax 64 (135 MB) 67 us in tiles, 59 with a wave
 // per class and patch, 35 here (3.9 TB/s).  At most KQ steps of four members, NT tiles of 16.
 template <int NT, int KQ>
-__global__ __launch_bounds__(256, KQ <= 9 ? 3 : 2) void rotation_stream(ThetaArgs a, int runs) {
-  extern __shared__ __attribute__((aligned(16))) double Ds[];
+__device__ __forceinline__ void rotation_block(const ThetaArgs &a, double *Ds, int l, int unit, int run, int runs) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r16 = lane & 15;
-  // largest degrees first, the unit of two classes (twice the work) first
-  const int run = blockIdx.x % runs, unit = (blockIdx.x / runs) % 3, l = a.L - blockIdx.x / (3 * runs);
   // l even: classes 1 and 2 trade, 0 and 3 stay; l odd: 0 and 3 trade
   const bool odd = l & 1, pair = unit == 0;
   const int c0 = pair ? (odd ? 0 : 1) : unit == 1 ? (odd ? 1 : 0) : (odd ? 2 : 3);
@@ -288,7 +320,27 @@ __global__ __launch_bounds__(256, KQ <= 9 ? 3 : 2) void rotation_stream(ThetaArg
   }
 }
 
+template <int NT, int KQ>
+__global__ __launch_bounds__(256, KQ <= 9 ? 3 : 2) void rotation_stream(ThetaArgs a, int runs) {
+  extern __shared__ __attribute__((aligned(16))) double Ds[];
+  // largest degrees first, the unit of two classes (twice the work) first
+  const int run = blockIdx.x % runs, unit = (blockIdx.x / runs) % 3;
+  rotation_block<NT, KQ>(a, Ds, a.L - blockIdx.x / (3 * runs), unit, run, runs);
+}
+
+// items (plan, 3 degree + unit, run, runs)
+template <int NT, int KQ>
+__global__ __launch_bounds__(256, KQ <= 9 ? 3 : 2) void rotation_group(const ThetaArgs *__restrict__ args,
+                                                                       const int4 *__restrict__ items) {
+  extern __shared__ __attribute__((aligned(16))) double Ds[];
+  const int4 it = items[blockIdx.x];
+  const ThetaArgs a = args[it.x];
+  rotation_block<NT, KQ>(a, Ds, it.y / 3, it.y % 3, it.z, it.w);
+}
+
 int even_tiles(int L) { return (L / 2 + 16) / 16; }
+
+constexpr int kGroupWaves = 4;  // waves of a batch's theta blocks
 
 // blocks of the theta kernels: chunks of row tiles per column, each of them
 // whole passes of the block's waves, about three blocks per CU
@@ -380,6 +432,42 @@ hipError_t launch_theta_stream(int phase, int variant, const ThetaArgs &a, int c
     case 2: return launch_rotation(a, variant ? 2 : 1, cus, s);
     case 3: return variant ? launch_theta_syn_w<4>(a, cus, s) : launch_theta_syn_w<8>(a, cus, s);
   }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_theta_group(int phase, int L, size_t lds, const ThetaArgs *args, const int4 *items, int n_items,
+                              hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid(n_items), block(phase == 2 ? 256 : 64 * kGroupWaves);
+  int nt, kq;
+  rotation_shape(L, &nt, &kq);
+#define YYG_COMMA ,
+#define YYG_GROUP(K)                                                            \
+  do {                                                                          \
+    hipLaunchKernelGGL((K), grid, block, lds, s, args, items);                  \
+    return hipGetLastError();                                                   \
+  } while (0)
+  if (phase == 1) switch (even_tiles(L)) {
+      case 1: YYG_GROUP(theta_ana_group<1 YYG_COMMA kGroupWaves>);
+      case 2: YYG_GROUP(theta_ana_group<2 YYG_COMMA kGroupWaves>);
+      case 3: YYG_GROUP(theta_ana_group<3 YYG_COMMA kGroupWaves>);
+    }
+  if (phase == 2) switch (kq) {
+      case 2: YYG_GROUP(rotation_group<1 YYG_COMMA 2>);
+      case 4: YYG_GROUP(rotation_group<1 YYG_COMMA 4>);
+      case 6: YYG_GROUP(rotation_group<2 YYG_COMMA 6>);
+      case 9: YYG_GROUP(rotation_group<3 YYG_COMMA 9>);
+      case 12: YYG_GROUP(rotation_group<3 YYG_COMMA 12>);
+    }
+  if (phase == 3) switch (theta_steps(L)) {
+      case 2: YYG_GROUP(theta_syn_group<2 YYG_COMMA kGroupWaves>);
+      case 4: YYG_GROUP(theta_syn_group<4 YYG_COMMA kGroupWaves>);
+      case 6: YYG_GROUP(theta_syn_group<6 YYG_COMMA kGroupWaves>);
+      case 10: YYG_GROUP(theta_syn_group<10 YYG_COMMA kGroupWaves>);
+      case 12: YYG_GROUP(theta_syn_group<12 YYG_COMMA kGroupWaves>);
+    }
+#undef YYG_GROUP
+#undef YYG_COMMA
   return hipErrorInvalidValue;
 }
 
