@@ -512,22 +512,22 @@ __global__ __launch_bounds__(256) void phi_syn_lean_kernel(PhiLeanArgs a) {
 // CMAX bounds the chunk length: the chunk loops unroll with every LDS read
 // at a clamped index, so that the reads issue ahead of the recurrences.
 // Column q of one plan's scan; waves p >= P (a one-patch plan in a block
-// sized for two) take part in the barriers only.  NCOL = 2: the block's
-// waves 0..P-1 scan column q, waves P..2P-1 column q2 of the same degree
-// (its recurrence coefficients staged once for both; q2 < 0: those waves
-// take part in the barriers only).
+// sized for two) take part in the barriers only.  NCOL > 1: the block's
+// waves P k .. P k + P - 1 scan column q + k of the same degree (its recurrence
+// coefficients staged once for all), k < cols <= NCOL; the other waves take
+// part in the barriers only.
 template <int CMAX, int NCOL = 1>
 __device__ __forceinline__ void radial_scan_q_body(const double *__restrict__ X, const double *__restrict__ coefS,
                                                    const int *__restrict__ qdeg, int nR, int L, int chunk,
                                                    double negG, double *__restrict__ Ut, int q, int P,
-                                                   double *smem, int q2 = -1) {
+                                                   double *smem, int cols = 1) {
   const int l = qdeg[q];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // (waves past NCOL P: a block sized for two patches with a plan of one)
   const int col = NCOL > 1 ? min(w / P, NCOL - 1) : 0, p = NCOL > 1 ? w - col * P : w;
-  const bool active = p < P && (col == 0 || q2 >= 0);
+  const bool active = p < P && col < cols;
   const int pa = p < P ? p : 0;                       // an inactive wave addresses patch 0 and stores nothing
-  if (col == 1 && q2 >= 0) q = q2;
+  if (col < cols) q += col;
   const long M = (long)P * nR;
   double *sc = smem;                                  // [4][nR]: c0, c1, c2, c3 over n
   // [nR + 1]: the moments, zero at nR; then the outputs
@@ -535,8 +535,9 @@ __device__ __forceinline__ void radial_scan_q_body(const double *__restrict__ X,
   {
     // staging: batches of CB coefficient and XB moment loads from clamped
     // addresses, all in flight before the first LDS store (one batch covers
-    // n_r <= 512 with two patches)
-    constexpr int CB = 16, XB = 8;
+    // the moments of n_r <= 1088; eight loads a batch took a second round of
+    // latency from 512 on: 550 shells, lmax 40 18.9 us, 17.1 here)
+    constexpr int CB = 16, XB = CMAX <= 17 ? CMAX + 1 : 8;
     const double *__restrict__ cl = coefS + (long)l * 4 * nR;
     const double *__restrict__ xp = X + (long)q * M + (long)pa * nR;
     const int nt = blockDim.x;
@@ -636,22 +637,28 @@ __global__ __launch_bounds__(128) void radial_scan_q_kernel(const double *__rest
   radial_scan_q_body<CMAX>(X, coefS, qdeg, nR, L, chunk, negG, Ut, blockIdx.x, blockDim.x / 64, smem);
 }
 
-// Two columns of one degree per block (P waves each): block b of degree l
-// (l (l + 1) / 2 <= b < (l + 1) (l + 2) / 2) takes columns l^2 + 2 j and
-// l^2 + 2 j + 1, j = b - l (l + 1) / 2, the second absent for j = l (the
-// degree's 2l + 1 columns are odd in number).
-template <int CMAX>
-__global__ __launch_bounds__(256) void radial_scan_q2_kernel(const double *__restrict__ X,
-                                                             const double *__restrict__ coefS,
-                                                             const int *__restrict__ qdeg, int nR, int L, int chunk,
-                                                             double negG, double *__restrict__ Ut, int P) {
+// The first block of degree l where every degree's 2l + 1 columns take
+// ceil((2l + 1) / NCOL) blocks, NCOL 2 or 4.
+template <int NCOL>
+__host__ __device__ __forceinline__ int scan_first_block(int l) {
+  return NCOL == 2 ? l * (l + 1) / 2 : l + (l - 1) * (l - 1) / 4;
+}
+
+// NCOL columns of one degree per block (P waves each), the coefficients
+// staged once for them: the j-th block of degree l takes the columns from
+// l^2 + NCOL j on.
+template <int CMAX, int NCOL>
+__global__ __launch_bounds__(128 * NCOL) void radial_scan_q_cols(const double *__restrict__ X,
+                                                                 const double *__restrict__ coefS,
+                                                                 const int *__restrict__ qdeg, int nR, int L, int chunk,
+                                                                 double negG, double *__restrict__ Ut, int P) {
   extern __shared__ double smem[];
   const int b = blockIdx.x;
-  int l = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-  while (l * (l + 1) / 2 > b) --l;            // exact for any rounding of the square root
-  while ((l + 1) * (l + 2) / 2 <= b) ++l;
-  const int j = b - l * (l + 1) / 2, q = l * l + 2 * j;
-  radial_scan_q_body<CMAX, 2>(X, coefS, qdeg, nR, L, chunk, negG, Ut, q, P, smem, j < l ? q + 1 : -1);
+  int l = (int)(NCOL == 2 ? (sqrt(8.0 * b + 1.0) - 1.0) * 0.5 : 2.0 * (sqrt(b + 1.0) - 1.0));
+  while (scan_first_block<NCOL>(l) > b) --l;  // exact for any rounding of the square root
+  while (scan_first_block<NCOL>(l + 1) <= b) ++l;
+  const int k = NCOL * (b - scan_first_block<NCOL>(l));
+  radial_scan_q_body<CMAX, NCOL>(X, coefS, qdeg, nR, L, chunk, negG, Ut, l * l + k, P, smem, min(NCOL, 2 * l + 1 - k));
 }
 
 // The same over the columns of several plans (batched separable solves): a
@@ -667,7 +674,7 @@ __global__ __launch_bounds__(128 * NCOL) void radial_scan_q_grouped(const ScanQA
   const ScanQArgs a = args[it.x];
   const int l = a.qdeg[it.y];
   radial_scan_q_body<CMAX, NCOL>(a.X, a.coefS, a.qdeg, a.nR, a.L, a.chunk, a.negG, a.Ut, it.y, a.P, smem,
-                                 NCOL > 1 && it.y + 1 < (l + 1) * (l + 1) ? it.y + 1 : -1);
+                                 min(NCOL, (l + 1) * (l + 1) - it.y));
 }
 
 // ---------------------------------------------------------------------------
@@ -1023,9 +1030,9 @@ hipError_t launch_expand_self_basis(const double *P, const double *Tr, int n_t, 
 
 size_t radial_scan_q_lds(int nR, int patches) { return (4UL * nR + (size_t)patches * (nR + 1UL)) * sizeof(double); }
 
-// the paired form: the coefficients once, two columns of every patch
-static size_t radial_scan_q2_lds(int nR, int patches) {
-  return (4UL * nR + 2UL * patches * (nR + 1UL)) * sizeof(double);
+// the coefficients once, `cols` columns of every patch
+static size_t radial_scan_cols_lds(int nR, int patches, int cols) {
+  return (4UL * nR + (size_t)cols * patches * (nR + 1UL)) * sizeof(double);
 }
 
 // the column and its coefficients fit in LDS and a lane's chunk in the
@@ -1033,6 +1040,48 @@ static size_t radial_scan_q2_lds(int nR, int patches) {
 bool radial_scan_q_supports(int nR, int patches) {
   return nR >= 1 && radial_scan_q_lds(nR, patches) <= kScanQMaxLds && (((nR + 63) / 64) | 1) <= 63;
 }
+
+namespace {
+
+// Columns per block: four waves' worth where they fit in LDS, so that the
+// coefficients are staged once for them, and where the blocks still fill the
+// device.  Two patches, two columns against one (us): 1000 shells, lmax 64 56
+// and 77, 550, 40 17 and 22; 400, 25 (351 blocks against 676) 11.4 and 10.6;
+// four columns 70 and 17.  One patch, four against two and one: 800 shells,
+// lmax 80 34, 47 and 92; 1000, 30 15, 17 and 21; 400, 25 10 all.
+int scan_columns(int nR, int Q, int patches) {
+  if (patches == 1 && Q >= 900 && radial_scan_cols_lds(nR, 1, 4) <= kScanQMaxLds) return 4;
+  return radial_scan_cols_lds(nR, patches, 2) <= kScanQMaxLds && Q >= 1024 ? 2 : 1;
+}
+
+template <int NCOL>
+hipError_t scan_cols(const double *X, const double *coefS, const int *qdeg, int nR, int L, double negG, int patches,
+                     double *Ut, hipStream_t s) {
+  const size_t lds = radial_scan_cols_lds(nR, patches, NCOL);
+  const int chunk = ((nR + 63) / 64) | 1;
+  if (lds > kScanQMaxLds) return hipErrorInvalidValue;
+  // instances close to the chunk (n_r 550: 9, n_r 1000: 17) keep the
+  // dependent recurrences short
+  auto go = [&](auto kern) {
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess)
+      return hipGetLastError();
+    hipLaunchKernelGGL(kern, dim3(scan_first_block<NCOL>(L + 1)), dim3(64 * NCOL * patches), lds, s, X, coefS, qdeg, nR,
+                       L, chunk, negG, Ut, patches);
+    return hipGetLastError();
+  };
+  if (chunk <= 7) return go(radial_scan_q_cols<7, NCOL>);
+  if (chunk <= 9) return go(radial_scan_q_cols<9, NCOL>);
+  if (chunk <= 11) return go(radial_scan_q_cols<11, NCOL>);
+  if (chunk <= 15) return go(radial_scan_q_cols<15, NCOL>);
+  if (chunk <= 17) return go(radial_scan_q_cols<17, NCOL>);
+  if (chunk <= 23) return go(radial_scan_q_cols<23, NCOL>);
+  if (chunk <= 31) return go(radial_scan_q_cols<31, NCOL>);
+  return go(radial_scan_q_cols<63, NCOL>);
+}
+
+}  // namespace
 
 hipError_t launch_radial_scan_q(const double *X, const double *coefS, const int *qdeg, int nR, int L, double negG,
                                 int patches, double *Ut, hipStream_t s) {
@@ -1050,33 +1099,9 @@ hipError_t launch_radial_scan_q(const double *X, const double *coefS, const int 
     hipLaunchKernelGGL(kern, dim3(Q), dim3(64 * patches), lds, s, X, coefS, qdeg, nR, L, chunk, negG, Ut);
     return hipGetLastError();
   };
-  // two columns per block where they fit in LDS (the coefficients staged
-  // once for both) ...; the unrolled chunk loops run CMAX steps: an instance
-  // close to the chunk (n_r 550: 9, n_r 1000: 17) keeps the dependent
-  // recurrences short
-  // (with enough columns: Q / 2 blocks must still fill the device; at
-  // lmax 25, 351 paired blocks ran slower than 676 single ones)
-  const size_t lds2 = radial_scan_q2_lds(nR, patches);
-  if (lds2 <= kScanQMaxLds && Q >= 1024) {
-    const int blocks = (L + 1) * (L + 2) / 2;
-    auto go2 = [&](auto kern) {
-      if (lds2 > 64 * 1024 &&
-          hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds2) != hipSuccess)
-        return hipGetLastError();
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(128 * patches), lds2, s, X, coefS, qdeg, nR, L, chunk, negG, Ut,
-                         patches);
-      return hipGetLastError();
-    };
-    if (chunk <= 7) return go2(radial_scan_q2_kernel<7>);
-    if (chunk <= 9) return go2(radial_scan_q2_kernel<9>);
-    if (chunk <= 11) return go2(radial_scan_q2_kernel<11>);
-    if (chunk <= 15) return go2(radial_scan_q2_kernel<15>);
-    if (chunk <= 17) return go2(radial_scan_q2_kernel<17>);
-    if (chunk <= 23) return go2(radial_scan_q2_kernel<23>);
-    if (chunk <= 31) return go2(radial_scan_q2_kernel<31>);
-    return go2(radial_scan_q2_kernel<63>);
-  }
+  const int cols = scan_columns(nR, Q, patches);
+  if (cols == 2) return scan_cols<2>(X, coefS, qdeg, nR, L, negG, patches, Ut, s);
+  if (cols == 4) return scan_cols<4>(X, coefS, qdeg, nR, L, negG, patches, Ut, s);
   if (chunk <= 7) return go(radial_scan_q_kernel<7>);
   if (chunk <= 9) return go(radial_scan_q_kernel<9>);
   if (chunk <= 11) return go(radial_scan_q_kernel<11>);
@@ -1090,12 +1115,12 @@ hipError_t launch_radial_scan_q(const double *X, const double *coefS, const int 
 
 // Three blocks of two columns and more fit a CU (up to 852 shells), and a
 // lane's chunk its instances.
-bool radial_scan_q_two(int max_nR) { return radial_scan_q2_lds(max_nR, 2) <= kScanQMaxLds / 3; }
+bool radial_scan_q_two(int max_nR) { return radial_scan_cols_lds(max_nR, 2, 2) <= kScanQMaxLds / 3; }
 
 hipError_t launch_radial_scan_q_grouped(const ScanQArgs *args, const int2 *items, int n_items, bool two, int max_nR,
                                         hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  const size_t lds = two ? radial_scan_q2_lds(max_nR, 2) : radial_scan_q_lds(max_nR, 2);
+  const size_t lds = two ? radial_scan_cols_lds(max_nR, 2, 2) : radial_scan_q_lds(max_nR, 2);
   if (lds > kScanQMaxLds) return hipErrorInvalidValue;
   const int chunk = ((max_nR + 63) / 64) | 1;
   auto go = [&](auto kern) {
