@@ -16,7 +16,9 @@ separable FP64 form).
 import argparse
 import hashlib
 import json
+import math
 import os
+import re
 import sys
 import time
 
@@ -31,7 +33,8 @@ SEP_LP = ("fp32", "bf16x3")   # reduced precisions of the separable form's phi t
 # every source a timed kernel is compiled from: counter figures taken on other sources are not used
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1806_04593_amd", "csrc", f)
                for f in ("yyg_internal.h", "yyg_tile.h", "yyg_kernels.hip", "yyg_kernels_x4.hip",
-                         "yyg_kernels_sep_lp.hip", "yyg_kernels_lp.hip", "yyg_batch_sep.hip", "yyg_phi_stream.hip")]
+                         "yyg_kernels_sep_lp.hip", "yyg_kernels_lp.hip", "yyg_batch_sep.hip", "yyg_phi_stream.hip",
+                         "yyg_phi_quad.hip", "yyg_theta.hip", "yyg_dense_fold.hip")]
 METRIC = "grid cells/sec per full Phi solve, FP64 vs split-precision, at stated max rel. error"
 
 
@@ -261,6 +264,21 @@ def phi_folded(kname):
                 or (kname.startswith("yyg::gemm_nt_f64_batched<") and int(args[-1]) & (128 | 256 | 4096)))
 
 
+def phi_share(kname, desc):
+    """The share of the unfolded multiply-adds a phi-transform kernel needs:
+    half for rows folded about the central meridian; folded about the
+    meridians 90 degrees off it too, the folded points over the cells (where
+    the spacing divides 180 degrees; else half)."""
+    if not re.search(r"::phi_(ana|syn)_(rows|quad)<", kname):
+        return 0.5 if phi_folded(kname) else 1.0
+    n_p = desc["n_phi"]
+    span = 2.0 * math.pi if desc.get("kind") == "polar" else 1.5 * math.pi + 2.0 * desc["delta_phi"]
+    c = n_p - 1 - math.pi * n_p / span
+    h, cc = (n_p + 1) // 2, round(c)
+    paired = abs(c - cc) < 1e-6 and 1 <= cc < h
+    return (h - (cc + 1) // 2 if paired else h) / n_p
+
+
 def phi_roofline(head, desc, M, nang):
     """Roofline of the dominant single-launch kernel of the separable solve,
     the longer phi transform."""
@@ -276,8 +294,7 @@ def phi_roofline(head, desc, M, nang):
     # per-phase events inside solves add a launch gap to each)
     ms_k = head["phase_alone_ms"][name]
     kname = head["kernel_names"][name]
-    if phi_folded(kname):
-        flops_k /= 2.0   # folded about the central meridian: half the multiply-adds
+    flops_k *= phi_share(kname, desc)
     tf = flops_k / (ms_k * 1e-3) / 1e12
     gbs = bytes_k / (ms_k * 1e-3) / 1e9
     fm, fh = tf / PEAK["fp64"], gbs / 8000.0
@@ -353,10 +370,9 @@ def bench_single(a):
         err = None if a.no_check else sampled_error(front, d_phi.cpu().numpy())
         L2 = 2 * desc["lmax"] + 1
         phi_flops = 2.0 * M * nang * L2           # each phi transform (unfolded count)
-        # algorithmic TFLOP/s of each phi transform in the solve (halved
-        # count for the folded kernels)
+        # algorithmic TFLOP/s of each phi transform in the solve
         names = {p: g.sep_kernel(q) for p, q in (("phi_analysis", 0), ("phi_synthesis", 4))}
-        alg = {p: phi_flops / (2.0 if phi_folded(n) else 1.0) for p, n in names.items()}
+        alg = {p: phi_flops * phi_share(n, desc) for p, n in names.items()}
         results["fp64_separable"] = {
             "cells_per_s": cells / (ms * 1e-3), "ms_per_step": ms, "max_rel_err_vs_oracle": err,
             "kernels_ms": {"phi_analysis": avg[4], "theta_analysis_rotation": avg[5], "radial_scan": avg[1],

@@ -70,8 +70,9 @@ struct GemmF64Args {
 //               (x = x0 + x1 + x2, each the rounding of the remainder) and the
 //               six part products of order < 3 on the 16x16x16 BF16 MFMA
 //  kGemmX4      v_mfma_f64_4x4x4f64 instead of the 16x16x4 form: measured on
-//               MI355X it runs at ~92% of the FP64 matrix peak where the
-//               16x16x4 form stops at ~62%, for four times the operand
+//               MI355X it runs at ~92% of the FP64 matrix peak (the 16x16x4
+//               form at ~98% with its accumulators in vector registers,
+//               62-76% in accumulation registers), for four times the operand
 //               traffic per flop (each 4 x 4 operand is replicated over the
 //               instruction's four blocks)
 enum {

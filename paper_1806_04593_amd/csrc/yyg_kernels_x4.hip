@@ -1,10 +1,10 @@
 // The separable form's contractions on v_mfma_f64_4x4x4f64 (kGemmX4).
 //
-// On MI355X (gfx950) the FP64 16x16x4 MFMA sustains about 49 TFLOP/s, 62%
-// of the 78.6 TFLOP/s FP64 matrix peak, while the 4x4x4 form (four
-// independent 4 x 4 x 4 products per instruction) sustains about 72 TFLOP/s
-// (measured with back-to-back independent instructions at 1-8 waves per
-// SIMD).  The price is operand traffic: each instruction reads one value per
+// On MI355X (gfx950) the 4x4x4 form (four independent 4 x 4 x 4 products per
+// instruction) sustains about 72 of the FP64 matrix peak's 78.6 TFLOP/s, the
+// 16x16x4 form 77 with its accumulators in vector registers and 48-60 in
+// accumulation registers (measured with back-to-back independent instructions
+// at 1-8 waves per SIMD).  The price is operand traffic: each instruction reads one value per
 // lane of each operand for a quarter of the 16x16x4 form's work, and the
 // four-wide side of every product is the same in all four blocks.  These
 // tiles keep that side narrow per wave (16 or 32) and the sixteen-wide side
