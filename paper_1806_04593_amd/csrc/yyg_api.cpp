@@ -859,8 +859,12 @@ void sep_default_phi(yyg_grid *g) {
   const int ana = yyg::phi_quad_default(true, S.quad_ana, g->cus);
   // without partners a short analysis gains nothing from the parity split:
   // 131 shells of 61 x 187 cells, lmax 23: 11.2 us in the 32 x 32 tiles, 11.6
-  // in the sweep
-  if (ana == 0 || S.quad_ana.T2 > 0) S.var[0] = base + ana;
+  // in the sweep; nor does one of fewer row tiles than four a CU, whose few
+  // waves each run every stage in turn (a solve, us: 100 shells of 90 x 180
+  // cells, one patch, lmax 12 29.5 and 30.6; 200 of 32 x 92, lmax 16 30.8 and
+  // 31.5; 400 of 47 x 137, 2350 row tiles, the sweep by 2)
+  const long tiles = (long)g->n_t * (((long)g->n_patch * g->n_r + 15) / 16);
+  if (ana == 0 || (S.quad_ana.T2 > 0 && tiles >= 4L * g->cus)) S.var[0] = base + ana;
   S.var[4] = base + yyg::phi_quad_default(false, S.quad_syn, g->cus);
 }
 
@@ -1129,8 +1133,13 @@ int sep_build(yyg_grid *g) {
   S.theta = yyg::ThetaArgs{S.X2,     S.TA, S.TS, S.Ut, S.DR, g->d_Ahat, S.At, S.V,
                            MJ,       (long)yyg::theta_ana_doubles(L, (nt + 1) / 2),
                            (long)yyg::theta_syn_doubles(L, (nt + 1) / 2), (long)yyg::rotation_doubles(L), L, g->n_r, (int)M, nt, (nt + 1) / 2};
+  // the theta synthesis' waves each run a column's colatitudes in turn: where
+  // they are few and the colatitudes many, 32 x 32 tiles (a solve, us: 25
+  // columns of 7 row tiles, 90 colatitudes 29.6 and 30.6; 41 of 13, 60 29.2
+  // and 30.0; 33 of 25, 32 colatitudes the same)
+  const bool few = (long)nmc * ((M + 15) / 16) < 3L * g->cus && nt > 48;
   for (int r = 1; r <= 3; ++r)
-    if (S.stream[r]) S.var[r] = yyg::gemm_f64_variant_count() + 4;
+    if (S.stream[r]) S.var[r] = r == 3 && few ? 10 : yyg::gemm_f64_variant_count() + 4;
   S.ready = true;
   return YYG_OK;
 }
