@@ -421,8 +421,7 @@ def bench_single(a):
         kms, kcnt = phase_pass(g, d_phi, prec, a)
         avg = [float(kms[i] / max(1, kcnt[i])) for i in range(4)]
         err = None if a.no_check else sampled_error(front, d_phi.cpu().numpy())
-        # FP64 contracts over a quarter patch (the plan's rule for the fold)
-        folded = (prec == "fp64" and desc["lmax"] >= 2 and M <= 65535 and M * nang * Q * (1 + P) >= 4e6)
+        folded = bool(g.plan_info(prec)["folded"])   # contracted over a quarter patch
         cells_syn = -(-desc["n_theta"] // 2) * -(-desc["n_phi"] // 2) if folded else nang
         flops_syn = 2.0 * M * cells_syn * (P * Q)
         achieved = flops_syn / (avg[2] * 1e-3) / 1e12

@@ -310,9 +310,10 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream);
  * YYG_ERR_NOT_READY for a reduced precision that is not prepared. */
 int yyg_plan_config(yyg_grid *g, int precision, int var_ana, int split_ana, int var_syn);
 
-/* Current launch configuration of one precision: info[0..6] = analysis
+/* Current launch configuration of one precision: info[0..7] = analysis
  * tile variant, its split-K factor, synthesis tile variant, analysis tile
- * rows/cols, synthesis tile rows/cols (first n entries are written). */
+ * rows/cols, synthesis tile rows/cols, 1 where the dense solve contracts
+ * over a quarter of the patch (first n entries are written). */
 int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n);
 
 /* Tile variant (numbered as for yyg_plan_info) of one phase of the

@@ -2580,8 +2580,8 @@ int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n) {
     yyg::gemm_f64_variant_tile(va, &ba, &bn_a);
     yyg::gemm_f64_variant_tile(vs, &bs, &bn_s);
   }
-  const int vals[7] = {va, sp, vs, ba, bn_a, bs, bn_s};
-  for (int i = 0; i < n && i < 7; ++i) info[i] = vals[i];
+  const int vals[8] = {va, sp, vs, ba, bn_a, bs, bn_s, !lp && g->fold.ready};
+  for (int i = 0; i < n && i < 8; ++i) info[i] = vals[i];
   return YYG_OK;
 }
 

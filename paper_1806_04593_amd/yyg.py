@@ -269,9 +269,9 @@ class Grid:
                "yyg_autotune")
 
     def plan_info(self, precision="fp64"):
-        info = (ctypes.c_int * 7)()
-        _check(lib().yyg_plan_info(self._h, PRECISIONS.get(precision, precision), info, 7), "yyg_plan_info")
-        keys = ("var_ana", "split_ana", "var_syn", "bm_ana", "bn_ana", "bm_syn", "bn_syn")
+        info = (ctypes.c_int * 8)()
+        _check(lib().yyg_plan_info(self._h, PRECISIONS.get(precision, precision), info, 8), "yyg_plan_info")
+        keys = ("var_ana", "split_ana", "var_syn", "bm_ana", "bn_ana", "bm_syn", "bn_syn", "folded")
         return dict(zip(keys, list(info)))
 
     def sep_config(self, phase, variant):
