@@ -298,8 +298,8 @@ int yyg_get_timing(yyg_grid *g, double *ms, long *counts, int n_slots);
  * or BF16 x 3: the tile shape of the reduced-precision phi transforms.  Allocates scratch memory for the
  * duration of the call and may grow the plan's partial-moment buffer.  With
  * the environment variable YYG_TUNE_CACHE naming a file, earlier choices
- * for the same (precision, shape) are read from it and new ones appended. A
- * folded dense plan's shape is that of its quarter patch.
+ * for the same (precision, shape) are read from it and new ones appended;
+ * a folded dense plan's entries (its quarter patch) are kept apart.
  * Without autotuning a plan uses a fixed heuristic.  Results do not depend
  * on the choice beyond FP64 summation order. */
 int yyg_autotune(yyg_grid *g, int precision, void *stream);

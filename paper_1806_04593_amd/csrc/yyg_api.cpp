@@ -2354,10 +2354,12 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
   };
   const char *cache_path = std::getenv("YYG_TUNE_CACHE");
   auto cache = read_tune_cache(cache_path);
-  // the folded solve contracts over a quarter patch: its own sizes name it
+  // the folded solve's four contractions over a quarter patch rank the tiles
+  // differently than one contraction of the same sizes: roles of their own
   const bool fold = !lp && g->fold.ready;
   const long cells = fold ? g->fold.hq : g->nang;
-  const std::string ka = tune_key(precision, 0, M, Q, cells), ks = tune_key(precision, 1, M, cells, (long)g->n_patch * Q);
+  const std::string ka = tune_key(precision, fold ? 2 : 0, M, Q, cells);
+  const std::string ks = tune_key(precision, fold ? 3 : 1, M, cells, (long)g->n_patch * Q);
   int best_va = *cur_va, best_sp = *cur_sp, best_vs = *cur_vs;
   // a plan in the separable form tunes that form's phases only (FP64): the
   // dense contractions keep their configuration
