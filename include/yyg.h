@@ -46,6 +46,13 @@
  *   that needed it releases what it had allocated.  Read at every
  *   allocation; unset, 0 or not a plain number: no cap.  Pinned host
  *   memory and the allocation-free solve's scratch array are not counted.
+ * - What a folded dense solve holds (see YYG_METHOD_DENSE) is kept within the
+ *   cap but not part of yyg_device_bytes, and gives way: an allocation of the
+ *   library that does not fit beside it, under the cap or on a full device,
+ *   takes it from plans of this process, the earliest first, after the
+ *   device's work.  Those plans solve unfolded from then on, until yyg_prepare
+ *   (FP64) or yyg_autotune.  A fold that another thread's call is using, or
+ *   that a solve was recorded with (stream capture), stays.
  */
 #ifndef YYG_H
 #define YYG_H
@@ -127,7 +134,8 @@ int yyg_grid_dims(const yyg_grid *g, int *n_r, int *n_theta, int *n_phi, int *Q)
  * plan.  Either output pointer may be NULL. */
 int yyg_grid_kind(const yyg_grid *g, int *kind, int *patches);
 
-/* Build the extra tables a reduced-precision path needs (no-op for FP64):
+/* Build the extra tables a reduced-precision path needs (FP64 in the dense
+ * form: the folded solve's, where the plan has none; never fails):
  * the analysis and synthesis bases split into 1 (FP32), 3 (BF16) or 2
  * (FP16) planes of the operand type, each basis row scaled by a power of
  * two.  Allocates; call before timing or capturing solves. */
@@ -143,6 +151,10 @@ int yyg_prepare(yyg_grid *g, int precision);
  *                        the two mirror symmetries: a quarter of that, for
  *                        one density-sized buffer and a quarter of the bases
  *                        more memory (unfolded where that is not to be had).
+ *                        These are allocated by the first of yyg_set_method
+ *                        (dense), yyg_prepare or yyg_autotune (FP64) and
+ *                        yyg_upload_rho outside a stream capture; switching
+ *                        to the separable form for the first time frees them.
  *  YYG_METHOD_SEPARABLE  the same sums factored along the tensor structure
  *                        of the tables: the analysis as a transform over phi
  *                        (w_jk C/S_k^(m), a GEMM per colatitude row) followed
@@ -226,7 +238,8 @@ int yyg_solve_noalloc(yyg_grid *g, const double *rho, double *phi, void *stream)
 int yyg_set_check_finite(yyg_grid *g, int on);
 
 /* Bytes of device memory the library holds in this process (plans, their
- * work buffers and batches; the figure YYG_MAX_DEVICE_BYTES caps). */
+ * work buffers and batches; the figure YYG_MAX_DEVICE_BYTES caps), without
+ * the buffers of folded dense solves, which give way to any other use. */
 int yyg_device_bytes(size_t *held);
 
 /* Debug/test export after a synchronised solve: the angular moments

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -34,10 +35,16 @@ long round_up(long v, long m) { return (v + m - 1) / m * m; }
 // the environment variable YYG_MAX_DEVICE_BYTES (a decimal byte count; unset,
 // empty, 0 or not a plain number: no cap), read at every allocation.  An
 // allocation that would take the total past the cap fails like a failed
-// hipMalloc, before the runtime is asked.
+// hipMalloc, before the runtime is asked.  The buffers of folded dense solves
+// (struct Fold) are spare: they are kept within the cap, but given up for any
+// other allocation that does not fit beside them, and not part of the figure.
 std::mutex g_mem_mu;
-std::unordered_map<void *, size_t> g_mem_sizes;
-size_t g_mem_held = 0;
+struct MemBlock {
+  size_t bytes;
+  bool spare;
+};
+std::unordered_map<void *, MemBlock> g_mem_blocks;
+size_t g_mem_held = 0, g_mem_spare = 0;
 
 size_t mem_cap() {
   const char *e = std::getenv("YYG_MAX_DEVICE_BYTES");
@@ -47,33 +54,49 @@ size_t mem_cap() {
   return (end && *end == '\0' && e[0] != '-') ? (size_t)v : 0;
 }
 
-hipError_t dev_malloc(void **p, size_t bytes) {
+// One attempt; *beside: it failed with spare blocks held, without which it
+// could fit.
+hipError_t dev_malloc_once(void **p, size_t bytes, bool spare, bool *beside) {
   std::lock_guard<std::mutex> lock(g_mem_mu);
   const size_t cap = mem_cap();
-  if (cap && (bytes > cap || g_mem_held > cap - bytes)) {
-    *p = nullptr;
-    return hipErrorOutOfMemory;
-  }
+  *p = nullptr;
+  *beside = false;
+  if (cap && (bytes > cap || g_mem_held > cap - bytes)) return hipErrorOutOfMemory;
+  *beside = g_mem_spare > 0;
+  if (cap && g_mem_held + g_mem_spare > cap - bytes) return hipErrorOutOfMemory;
   const hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     *p = nullptr;
     return e;
   }
   if (*p) {
-    g_mem_sizes[*p] = bytes;
-    g_mem_held += bytes;
+    g_mem_blocks[*p] = MemBlock{bytes, spare};
+    (spare ? g_mem_spare : g_mem_held) += bytes;
   }
   return hipSuccess;
+}
+
+// The buffers of one folded dense solve are given up; false: none can be.
+bool fold_reclaim();
+
+hipError_t dev_malloc(void **p, size_t bytes) {
+  bool beside;
+  hipError_t e = dev_malloc_once(p, bytes, false, &beside);
+  while (e == hipErrorOutOfMemory && beside && fold_reclaim()) {
+    (void)hipGetLastError();
+    e = dev_malloc_once(p, bytes, false, &beside);
+  }
+  return e;
 }
 
 hipError_t dev_free(void *p) {
   if (!p) return hipSuccess;
   {
     std::lock_guard<std::mutex> lock(g_mem_mu);
-    auto it = g_mem_sizes.find(p);
-    if (it != g_mem_sizes.end()) {
-      g_mem_held -= it->second;
-      g_mem_sizes.erase(it);
+    auto it = g_mem_blocks.find(p);
+    if (it != g_mem_blocks.end()) {
+      (it->second.spare ? g_mem_spare : g_mem_held) -= it->second.bytes;
+      g_mem_blocks.erase(it);
     }
   }
   return hipFree(p);
@@ -120,14 +143,23 @@ struct yyg_grid {
   bool ahat_fold = false;  // d_Ahat's columns are in the fold's order
 
   // dense FP64 solve folded about both mirror planes (yyg_dense_fold.hip);
-  // class c holds columns cols[co[c] .. co[c] + N[c])
+  // class c holds columns cols[co[c] .. co[c] + N[c]).  Built where a density
+  // is handed to a plan in the dense form, the form is chosen or FP64 prepared
+  // or tuned (fold_try), so that plans of another form do not hold it, and
+  // given back when memory runs short (fold_reclaim).
   struct Fold {
-    bool ready = false;
+    std::atomic<bool> ready{false};  // the solve runs folded
+    std::atomic<bool> tried{false};  // built, not to be had, or given back for memory: only asked for again
+    bool captured = false;   // a recorded graph holds the buffers: kept to the plan's end
+    int users = 0;           // calls on this plan that use them now
+    int var_ana = 0, var_syn = 0, nsplit = 1;  // the contractions' tiles and split
+    int splits = 0;          // splits that part holds
+    double *part = nullptr;  // partial moments, where d_part holds fewer splits than nsplit
     long hq = 0;             // cells of a quarter patch
     long ldb = 0, ldy[4] = {};
     int N[4] = {}, co[4] = {};  // columns of a class, first one
     int K[4] = {}, ko[4] = {};  // synthesis contraction length of a class, first column in U
-    std::vector<int> cols;   // column q at each place
+    std::vector<int> cols;   // column q at each place (kept when the buffers go: ahat_fold)
     int *d_cols = nullptr, *d_deg = nullptr;
     int2 *d_ucol = nullptr;
     double *Bt = nullptr;    // [Q][ldb]
@@ -255,17 +287,95 @@ void lp_release(LpPlan &l) {
   }
 }
 
-void fold_release(yyg_grid *g) {
+// Plans whose fold is built, the oldest first.  The lock covers this list and
+// the state of every fold in it; it is held over no launch and no table build.
+std::mutex g_fold_mu;
+std::vector<yyg_grid *> g_folds;
+
+// Free a fold's buffers (under g_fold_mu once it is in the list).
+void fold_free(yyg_grid *g) {
   auto &f = g->fold;
-  void *b[] = {f.d_cols, f.d_deg, f.d_ucol, f.Bt, f.Y[0], f.Y[1], f.Y[2], f.Y[3], f.F};
+  void *b[] = {f.d_cols, f.d_deg, f.d_ucol, f.Bt, f.Y[0], f.Y[1], f.Y[2], f.Y[3], f.F, f.part};
   for (void *x : b)
     if (x) (void)dev_free(x);
-  f = yyg_grid::Fold{};
+  f.d_cols = f.d_deg = nullptr;
+  f.d_ucol = nullptr;
+  f.Bt = f.F = f.part = nullptr;
+  for (double *&y : f.Y) y = nullptr;
+  f.splits = 0;
+  f.ready = false;
 }
+
+// Give back a fold that no call uses and no recorded graph holds, after the
+// work on its device (under g_fold_mu).
+bool fold_drop(yyg_grid *g) {
+  auto &f = g->fold;
+  if (!f.ready || f.users > 0 || f.captured) return false;
+  DeviceGuard dg(g->device);
+  if (!dg.ok || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  fold_free(g);
+  g_folds.erase(std::remove(g_folds.begin(), g_folds.end(), g), g_folds.end());
+  return true;
+}
+
+bool fold_reclaim() {
+  std::lock_guard<std::mutex> lock(g_fold_mu);
+  for (yyg_grid *g : g_folds)
+    if (fold_drop(g)) return true;
+  return false;
+}
+
+// A plan's own fold, given back if it can be; `again`: to be built again when
+// the dense form is next used.
+void fold_release(yyg_grid *g, bool again) {
+  std::lock_guard<std::mutex> lock(g_fold_mu);
+  if (fold_drop(g) && again) g->fold.tried = false;
+}
+
+// Whether s is being recorded into a graph (the default stream cannot be).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (s && hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;  // not known
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// The fold of one call, held until the call has enqueued its work; `s` is the
+// stream it goes to.
+struct FoldUse {
+  yyg_grid *g = nullptr;
+  FoldUse(yyg_grid *plan, hipStream_t s) {
+    if (!plan) return;
+    std::lock_guard<std::mutex> lock(g_fold_mu);
+    if (!plan->fold.ready) return;
+    plan->fold.captured = plan->fold.captured || capturing(s);
+    plan->fold.users += 1;
+    g = plan;
+  }
+  void end() {
+    if (!g) return;
+    std::lock_guard<std::mutex> lock(g_fold_mu);
+    g->fold.users -= 1;
+    g = nullptr;
+  }
+  explicit operator bool() const { return g != nullptr; }
+  ~FoldUse() { end(); }
+  FoldUse(const FoldUse &) = delete;
+  FoldUse &operator=(const FoldUse &) = delete;
+};
 
 void free_grid(yyg_grid *g) {
   if (!g) return;
-  fold_release(g);
+  {
+    std::lock_guard<std::mutex> lock(g_fold_mu);
+    fold_free(g);
+    g_folds.erase(std::remove(g_folds.begin(), g_folds.end(), g), g_folds.end());
+  }
   double *bufs[] = {g->d_Bt, g->d_Y, g->d_coef, g->d_part, g->d_Ahat, g->d_U, g->d_rho_owned};
   (void)dev_free(g->d_flag);
   for (double *b : bufs)
@@ -408,77 +518,117 @@ bool fold_wanted(const yyg_grid *g) {
   return g->L >= 2 && M <= 65535 && (double)M * g->nang * g->Q * (1 + g->n_patch) >= kFoldMinMacs;
 }
 
-// The fold's tables.  False (not wanted, memory short, or a table without the
-// symmetry): the plan solves unfolded.
-bool fold_build(yyg_grid *g) {
+// The fold's tables, built on a stream of their own (no other stream has to
+// wait, and a capture under way elsewhere is not disturbed).  No other fold is
+// given up for this one.  False (not wanted, memory short, or a table without
+// the symmetry): the plan solves unfolded.
+bool fold_build(yyg_grid *g, hipStream_t s) {
   auto &f = g->fold;
   const int Q = g->Q, P = g->n_patch;
   const long M = (long)P * g->n_r;
-  if (!fold_wanted(g)) return false;
   f.hq = fold_cells(g);
   f.ldb = round_up(f.hq, 16);
-  std::vector<int> deg, ycols;
+  std::vector<int> deg, ycols, cols;
   std::vector<int2> ucol;
   int yo[4];
   const auto swapped = [](int c) { return (c >> 1) | (c & 1) << 1; };
   try {
     const auto tab = yyg::column_table(g->L);
     for (int c = 0; c < 4; ++c) {
-      f.co[c] = (int)f.cols.size();
+      f.co[c] = (int)cols.size();
       for (int q = 0; q < Q; ++q)
-        if ((((tab[q].l + tab[q].m) & 1) << 1 | (tab[q].is_sin ? 1 : 0)) == c) f.cols.push_back(q);
-      f.N[c] = (int)f.cols.size() - f.co[c];
+        if ((((tab[q].l + tab[q].m) & 1) << 1 | (tab[q].is_sin ? 1 : 0)) == c) cols.push_back(q);
+      f.N[c] = (int)cols.size() - f.co[c];
     }
     for (int c = 0, at = 0; c < 4; at += f.K[c++]) {
       f.ko[c] = at;
       f.K[c] = f.N[c] + (P == 2 ? f.N[swapped(c)] : 0);
       f.ldy[c] = round_up(f.K[c], 16);
       yo[c] = (int)ycols.size();
-      for (int i = 0; i < f.N[c]; ++i) ycols.push_back(f.cols[f.co[c] + i]);
-      for (int i = 0; P == 2 && i < f.N[swapped(c)]; ++i) ycols.push_back(Q + f.cols[f.co[swapped(c)] + i]);
+      for (int i = 0; i < f.N[c]; ++i) ycols.push_back(cols[f.co[c] + i]);
+      for (int i = 0; P == 2 && i < f.N[swapped(c)]; ++i) ycols.push_back(Q + cols[f.co[swapped(c)] + i]);
     }
     for (int c = 0; c < 4; ++c)
       for (int i = 0; i < f.N[c]; ++i) {
-        deg.push_back(tab[f.cols[f.co[c] + i]].l);
+        deg.push_back(tab[cols[f.co[c] + i]].l);
         ucol.push_back(int2{f.ko[c] + i, f.ko[swapped(c)] + f.N[swapped(c)] + i});
       }
   } catch (const std::bad_alloc &) {
     return false;
   }
   int *d_ycols = nullptr, *d_flag = nullptr;
-  int st = dmalloc(&f.d_cols, (size_t)Q);
-  if (st == YYG_OK) st = dmalloc(&f.d_deg, (size_t)Q);
-  if (st == YYG_OK) st = dmalloc(&f.d_ucol, (size_t)Q);
-  if (st == YYG_OK) st = dmalloc(&f.Bt, (size_t)Q * f.ldb);
-  for (int c = 0; c < 4 && st == YYG_OK; ++c) st = dmalloc(&f.Y[c], (size_t)f.hq * f.ldy[c]);
-  if (st == YYG_OK) st = dmalloc(&f.F, (size_t)4 * M * f.hq);
-  if (st == YYG_OK) st = dmalloc(&d_ycols, ycols.size());
-  if (st == YYG_OK) st = dmalloc(&d_flag, 1);
+  auto take = [](auto **p, size_t n) {
+    bool beside;
+    if (dev_malloc_once(reinterpret_cast<void **>(p), n * sizeof(**p), true, &beside) == hipSuccess) return YYG_OK;
+    (void)hipGetLastError();
+    return YYG_ERR_OUT_OF_MEMORY;
+  };
+  int st = take(&f.d_cols, (size_t)Q);
+  if (st == YYG_OK) st = take(&f.d_deg, (size_t)Q);
+  if (st == YYG_OK) st = take(&f.d_ucol, (size_t)Q);
+  if (st == YYG_OK) st = take(&f.Bt, (size_t)Q * f.ldb);
+  for (int c = 0; c < 4 && st == YYG_OK; ++c) st = take(&f.Y[c], (size_t)f.hq * f.ldy[c]);
+  if (st == YYG_OK) st = take(&f.F, (size_t)4 * M * f.hq);
+  if (st == YYG_OK && f.nsplit > g->part_cap) {
+    st = take(&f.part, (size_t)f.nsplit * M * Q);
+    f.splits = f.nsplit;
+  }
+  if (st == YYG_OK) st = take(&d_ycols, ycols.size());
+  if (st == YYG_OK) st = take(&d_flag, 1);
   hipError_t e = st == YYG_OK ? hipSuccess : hipErrorOutOfMemory;
   auto chk = [&](hipError_t r) {
     if (e == hipSuccess && r != hipSuccess) e = r;
   };
   int bad = 0;
   if (e == hipSuccess) {
-    chk(hipMemcpy(f.d_cols, f.cols.data(), Q * sizeof(int), hipMemcpyHostToDevice));
-    chk(hipMemcpy(f.d_deg, deg.data(), Q * sizeof(int), hipMemcpyHostToDevice));
-    chk(hipMemcpy(f.d_ucol, ucol.data(), Q * sizeof(int2), hipMemcpyHostToDevice));
-    chk(hipMemcpy(d_ycols, ycols.data(), ycols.size() * sizeof(int), hipMemcpyHostToDevice));
-    chk(hipMemcpy(d_flag, &bad, sizeof(int), hipMemcpyHostToDevice));
+    chk(hipMemcpyAsync(f.d_cols, cols.data(), Q * sizeof(int), hipMemcpyHostToDevice, s));
+    chk(hipMemcpyAsync(f.d_deg, deg.data(), Q * sizeof(int), hipMemcpyHostToDevice, s));
+    chk(hipMemcpyAsync(f.d_ucol, ucol.data(), Q * sizeof(int2), hipMemcpyHostToDevice, s));
+    chk(hipMemcpyAsync(d_ycols, ycols.data(), ycols.size() * sizeof(int), hipMemcpyHostToDevice, s));
+    chk(hipMemcpyAsync(d_flag, &bad, sizeof(int), hipMemcpyHostToDevice, s));
     for (int c = 0; c < 4 && e == hipSuccess; ++c) {
       chk(yyg::launch_fold_analysis_basis(g->d_Bt, g->ldb, f.d_cols + f.co[c], f.N[c], c, g->n_t, g->n_p,
-                                          f.Bt + f.co[c] * f.ldb, f.ldb, d_flag, 0));
+                                          f.Bt + f.co[c] * f.ldb, f.ldb, d_flag, s));
       chk(yyg::launch_fold_synthesis_basis(g->d_Y, g->ldy, d_ycols + yo[c], f.K[c], c, g->n_t, g->n_p, f.Y[c],
-                                           f.ldy[c], d_flag, 0));
+                                           f.ldy[c], d_flag, s));
     }
-    chk(hipMemcpy(&bad, d_flag, sizeof(int), hipMemcpyDeviceToHost));
+    chk(hipMemcpyAsync(&bad, d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
+    chk(hipStreamSynchronize(s));
   }
   if (d_ycols) (void)dev_free(d_ycols);
   if (d_flag) (void)dev_free(d_flag);
   if (e != hipSuccess) (void)hipGetLastError();
-  f.ready = e == hipSuccess && bad == 0;
-  return f.ready;
+  if (e == hipSuccess && bad == 0) f.cols.swap(cols);
+  return e == hipSuccess && bad == 0;
 }
+
+// Build the fold of a plan that has none.
+void fold_try(yyg_grid *g) {
+  auto &f = g->fold;
+  if (f.ready || !fold_wanted(g)) return;
+  DeviceGuard dg(g->device);
+  if (!dg.ok) return;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  hipStream_t s = nullptr;
+  bool ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
+  if (ok) {
+    ok = fold_build(g, s);
+    (void)hipStreamDestroy(s);
+  }
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  (void)hipGetLastError();
+  std::lock_guard<std::mutex> lock(g_fold_mu);
+  f.tried = true;
+  if (ok) try {
+      g_folds.push_back(g);
+    } catch (const std::bad_alloc &) {
+      ok = false;
+    }
+  if (!ok) fold_free(g);
+  f.ready = ok;
+}
+
 
 // The four classes' analysis contractions over the folded densities in F;
 // part [nsplit][M][Q], columns in the fold's order.
@@ -1776,16 +1926,12 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
                                       : yyg::make_patch(g->n_t, g->n_p, d->delta_theta, d->delta_phi);
   const int L = g->L, Q = g->Q, n_r = g->n_r;
   const long M = (long)g->n_patch * n_r;
-  int fold_split = 1, fold_ana = 0, fold_syn = 0;
   {
     int bm, bn;
     yyg::gemm_f64_variant_tile(g->var_ana, &bm, &bn);
     g->nsplit = yyg::choose_split(((M + bm - 1) / bm) * ((Q + bn - 1) / bn), g->nang);
     g->part_cap = g->nsplit;
-    if (fold_wanted(g)) {
-      fold_shape(g, &fold_ana, &fold_syn, &fold_split);
-      g->part_cap = std::max(g->part_cap, fold_split);
-    }
+    if (fold_wanted(g)) fold_shape(g, &g->fold.var_ana, &g->fold.var_syn, &g->fold.nsplit);
   }
 
   std::vector<double> Tt, CS, coef, P, Tr, Yx;
@@ -1879,12 +2025,6 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
     free_grid(g);
     return YYG_ERR_DEVICE;
   }
-  if (!fold_build(g)) fold_release(g);  // the unfolded solve runs instead
-  if (g->fold.ready) {
-    g->nsplit = fold_split;
-    g->var_ana = fold_ana;
-    g->var_syn = fold_syn;
-  }
   *out = g;
   return YYG_OK;
 }
@@ -1921,7 +2061,10 @@ int yyg_grid_kind(const yyg_grid *g, int *kind, int *patches) {
 
 int yyg_prepare(yyg_grid *g, int precision) {
   if (!g) return YYG_ERR_INVALID_ARG;
-  if (precision == YYG_FP64) return YYG_OK;
+  if (precision == YYG_FP64) {
+    if (g->method == YYG_METHOD_DENSE) fold_try(g);
+    return YYG_OK;
+  }
   if (precision < 0 || precision > YYG_FP16X2) return YYG_ERR_INVALID_ARG;
   auto &L = g->lp[precision - 1];
   if (L.ready) return YYG_OK;
@@ -1992,6 +2135,8 @@ int yyg_prepare(yyg_grid *g, int precision) {
 
 int yyg_upload_rho(yyg_grid *g, const double *rho, int rho_is_device, void *stream) {
   if (!g || !rho) return YYG_ERR_INVALID_ARG;
+  // the solve that follows cannot allocate
+  if (g->method == YYG_METHOD_DENSE && !g->fold.tried && fold_wanted(g) && !capturing(as_stream(stream))) fold_try(g);
   if (rho_is_device) {
     g->rho = rho;
     return YYG_OK;
@@ -2062,9 +2207,10 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
     return YYG_OK;
   }
   g->ahat_cols = false;
-  const bool fold = !lp && g->fold.ready;
-  g->ahat_fold = fold;
-  const int nsplit = lp ? g->lp[precision - 1].nsplit : g->nsplit;
+  FoldUse fold(lp ? nullptr : g, s);
+  g->ahat_fold = (bool)fold;
+  const int nsplit = lp ? g->lp[precision - 1].nsplit : fold ? g->fold.nsplit : g->nsplit;
+  double *part = fold && nsplit > g->part_cap ? g->fold.part : g->d_part;
   if (lp) {
     // split the density into operand planes (rows scaled for FP16)
     const auto &L = g->lp[precision - 1];
@@ -2079,7 +2225,7 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
     t = timing_begin(g, 0, s);
     if (fold) {
       e = yyg::launch_fold_rows(g->rho, g->fold.F, (int)M, g->n_t, g->n_p, s);
-      if (e == hipSuccess) e = fold_analysis(g, g->var_ana, nsplit, g->d_part, s);
+      if (e == hipSuccess) e = fold_analysis(g, g->fold.var_ana, nsplit, part, s);
     } else if (!lp) {
       e = yyg::launch_gemm_nt_f64(g->var_ana, 0, (int)M, Q, (int)g->nang, g->rho, g->nang, g->d_Bt, g->ldb,
                                   g->d_part, Q, nsplit, M * Q, s);
@@ -2093,7 +2239,7 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
   }
   if (e == hipSuccess) {
     t = timing_begin(g, 1, s);
-    e = yyg::launch_radial_scan(g->d_part, nsplit, M * Q, g->d_Ahat, g->d_coef, fold ? g->fold.d_deg : g->d_qdeg, n_r,
+    e = yyg::launch_radial_scan(part, nsplit, M * Q, g->d_Ahat, g->d_coef, fold ? g->fold.d_deg : g->d_qdeg, n_r,
                                 Q, g->L, -g->G, g->d_U, g->ldy, g->n_patch, s, fold ? g->fold.d_ucol : nullptr);
     timing_end(g, t, s);
   }
@@ -2109,7 +2255,7 @@ int yyg_solve(yyg_grid *g, double *phi, int phi_is_device, int precision, void *
   if (e == hipSuccess) {
     t = timing_begin(g, 2, s);
     if (fold) {
-      e = fold_synthesis(g, g->var_syn, s);
+      e = fold_synthesis(g, g->fold.var_syn, s);
       if (e == hipSuccess) e = yyg::launch_unfold_rows(g->fold.F, out, (int)M, g->n_t, g->n_p, s);
     } else if (!lp) {
       e = yyg::launch_gemm_nt_f64(g->var_syn, 1, (int)M, (int)g->nang, g->n_patch * Q, g->d_U, g->ldy, g->d_Y, g->ldy, out,
@@ -2287,8 +2433,10 @@ int yyg_set_method(yyg_grid *g, int method) {
     }
     int st = sep_build(g);
     if (st != YYG_OK) return st;
+    fold_release(g, true);  // a plan that goes back to the dense form builds it again and keeps it
   }
   g->method = method;
+  if (method == YYG_METHOD_DENSE && !g->fold.tried) fold_try(g);
   return YYG_OK;
 }
 
@@ -2342,9 +2490,6 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
   }
   const int Q = g->Q;
   const long M = (long)g->n_patch * g->n_r;
-  int *cur_va = lp ? &g->lp[precision - 1].var_ana : &g->var_ana;
-  int *cur_sp = lp ? &g->lp[precision - 1].nsplit : &g->nsplit;
-  int *cur_vs = lp ? &g->lp[precision - 1].var_syn : &g->var_syn;
   const int nv = lp ? yyg::gemm_lp_variant_count() : yyg::gemm_f64_variant_count();
   auto tile = [&](int v, int *bm, int *bn) {
     if (lp)
@@ -2354,40 +2499,52 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
   };
   const char *cache_path = std::getenv("YYG_TUNE_CACHE");
   auto cache = read_tune_cache(cache_path);
-  // the folded solve's four contractions over a quarter patch rank the tiles
-  // differently than one contraction of the same sizes: roles of their own
-  const bool fold = !lp && g->fold.ready;
-  const long cells = fold ? g->fold.hq : g->nang;
-  const std::string ka = tune_key(precision, fold ? 2 : 0, M, Q, cells);
-  const std::string ks = tune_key(precision, fold ? 3 : 1, M, cells, (long)g->n_patch * Q);
-  int best_va = *cur_va, best_sp = *cur_sp, best_vs = *cur_vs;
   // a plan in the separable form tunes that form's phases only (FP64): the
   // dense contractions keep their configuration
   const bool sep_only = !lp && sep_form;
-  bool have_a = sep_only, have_s = sep_only;
-  if (!sep_only && cache.count(ka)) {
-    best_va = cache[ka].first;
-    best_sp = cache[ka].second;
-    have_a = best_va >= 0 && best_va < nv && best_sp >= 1 && best_sp <= 32;
-  }
-  if (!sep_only && cache.count(ks)) {
-    best_vs = cache[ks].first;
-    have_s = best_vs >= 0 && best_vs < nv;
-  }
+  if (!lp && !sep_only) fold_try(g);
+  FoldUse fold(lp || sep_only ? nullptr : g, s);
   double *tmp_in = nullptr, *tmp_out = nullptr, *tmp_part = nullptr;
   const int smax = 32;
-  int st = YYG_OK;
-  if (!have_a || !have_s) {
-    if (!g->rho) st = dmalloc(&tmp_in, (size_t)M * g->nang);
-    if (st == YYG_OK) st = dmalloc(&tmp_out, (size_t)M * g->nang);
-    if (st == YYG_OK) st = dmalloc(&tmp_part, (size_t)smax * M * Q);
-    if (st == YYG_OK && tmp_in) (void)hipMemsetAsync(tmp_in, 0, (size_t)M * g->nang * sizeof(double), s);
-    if (st != YYG_OK) {
-      if (tmp_in) (void)dev_free(tmp_in);
-      if (tmp_out) (void)dev_free(tmp_out);
-      if (tmp_part) (void)dev_free(tmp_part);
-      return st;
+  long cells = 0;
+  std::string ka, ks;
+  int best_va = 0, best_sp = 1, best_vs = 0;
+  bool have_a = sep_only, have_s = sep_only;
+  for (int st = YYG_ERR_OUT_OF_MEMORY; st != YYG_OK;) {
+    // the folded solve's four contractions over a quarter patch rank the
+    // tiles differently than one contraction of the same sizes: roles of
+    // their own
+    cells = fold ? g->fold.hq : g->nang;
+    ka = tune_key(precision, fold ? 2 : 0, M, Q, cells);
+    ks = tune_key(precision, fold ? 3 : 1, M, cells, (long)g->n_patch * Q);
+    best_va = lp ? g->lp[precision - 1].var_ana : fold ? g->fold.var_ana : g->var_ana;
+    best_sp = lp ? g->lp[precision - 1].nsplit : fold ? g->fold.nsplit : g->nsplit;
+    best_vs = lp ? g->lp[precision - 1].var_syn : fold ? g->fold.var_syn : g->var_syn;
+    if (!sep_only && cache.count(ka)) {
+      best_va = cache[ka].first;
+      best_sp = cache[ka].second;
+      have_a = best_va >= 0 && best_va < nv && best_sp >= 1 && best_sp <= 32;
     }
+    if (!sep_only && cache.count(ks)) {
+      best_vs = cache[ks].first;
+      have_s = best_vs >= 0 && best_vs < nv;
+    }
+    if (have_a && have_s) break;
+    // (the folded contractions run in the fold's own buffers)
+    st = dmalloc(&tmp_part, (size_t)smax * M * Q);
+    if (!fold && st == YYG_OK && !g->rho) st = dmalloc(&tmp_in, (size_t)M * g->nang);
+    if (!fold && st == YYG_OK) st = dmalloc(&tmp_out, (size_t)M * g->nang);
+    if (st == YYG_OK && tmp_in) (void)hipMemsetAsync(tmp_in, 0, (size_t)M * g->nang * sizeof(double), s);
+    if (st == YYG_OK) break;
+    for (double **t : {&tmp_in, &tmp_out, &tmp_part}) {
+      if (*t) (void)dev_free(*t);
+      *t = nullptr;
+    }
+    if (!fold) return st;
+    fold.end();
+    fold_release(g, false);
+    if (g->fold.ready) return st;  // in a recorded graph
+    have_a = have_s = false;       // unfolded, with the fold's memory
   }
   const double *rho = g->rho ? g->rho : tmp_in;
   const bool scaled = precision == YYG_FP16X2;
@@ -2457,18 +2614,23 @@ int yyg_autotune(yyg_grid *g, int precision, void *stream) {
   if (tmp_in) (void)dev_free(tmp_in);
   if (tmp_out) (void)dev_free(tmp_out);
   if (tmp_part) (void)dev_free(tmp_part);
-  if (best_sp > g->part_cap) {
+  if (best_sp > std::max(g->part_cap, fold ? g->fold.splits : 0)) {
     double *np = nullptr;
-    if (dmalloc(&np, (size_t)best_sp * M * Q) != YYG_OK) return YYG_ERR_OUT_OF_MEMORY;
-    (void)hipDeviceSynchronize();
-    (void)dev_free(g->d_part);
-    g->d_part = np;
-    g->part_gen += 1;
-    g->part_cap = best_sp;
+    if (dmalloc(&np, (size_t)best_sp * M * Q) == YYG_OK) {
+      (void)hipDeviceSynchronize();
+      (void)dev_free(g->d_part);
+      g->d_part = np;
+      g->part_gen += 1;
+      g->part_cap = best_sp;
+    } else if (fold) {
+      best_sp = g->fold.nsplit;
+    } else {
+      return YYG_ERR_OUT_OF_MEMORY;
+    }
   }
-  *cur_va = best_va;
-  *cur_sp = best_sp;
-  *cur_vs = best_vs;
+  (lp ? g->lp[precision - 1].var_ana : fold ? g->fold.var_ana : g->var_ana) = best_va;
+  (lp ? g->lp[precision - 1].nsplit : fold ? g->fold.nsplit : g->nsplit) = best_sp;
+  (lp ? g->lp[precision - 1].var_syn : fold ? g->fold.var_syn : g->var_syn) = best_vs;
   // separable form (FP64): tile variant of each grouped phase
   if (sep_only && g->sep.ready) {
     double *phi_t = nullptr, *rho_t = nullptr;
@@ -2558,9 +2720,9 @@ int yyg_plan_config(yyg_grid *g, int precision, int var_ana, int split_ana, int 
     L.nsplit = split_ana;
     L.var_syn = var_syn;
   } else {
-    g->var_ana = var_ana;
-    g->nsplit = split_ana;
-    g->var_syn = var_syn;
+    g->var_ana = g->fold.var_ana = var_ana;
+    g->nsplit = g->fold.nsplit = split_ana;
+    g->var_syn = g->fold.var_syn = var_syn;
   }
   return YYG_OK;
 }
@@ -2569,6 +2731,16 @@ int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n) {
   if (!g || !info || n < 1 || precision < 0 || precision > YYG_FP16X2) return YYG_ERR_INVALID_ARG;
   const bool lp = precision != YYG_FP64;
   int va = g->var_ana, sp = g->nsplit, vs = g->var_syn;
+  bool folded;
+  {
+    std::lock_guard<std::mutex> lock(g_fold_mu);
+    folded = !lp && g->fold.ready;
+    if (folded || (fold_wanted(g) && !g->fold.tried)) {  // or to be built
+      va = g->fold.var_ana;
+      sp = g->fold.nsplit;
+      vs = g->fold.var_syn;
+    }
+  }
   if (lp) {
     va = g->lp[precision - 1].var_ana;
     sp = g->lp[precision - 1].nsplit;
@@ -2582,7 +2754,7 @@ int yyg_plan_info(const yyg_grid *g, int precision, int *info, int n) {
     yyg::gemm_f64_variant_tile(va, &ba, &bn_a);
     yyg::gemm_f64_variant_tile(vs, &bs, &bn_s);
   }
-  const int vals[8] = {va, sp, vs, ba, bn_a, bs, bn_s, !lp && g->fold.ready};
+  const int vals[8] = {va, sp, vs, ba, bn_a, bs, bn_s, folded};
   for (int i = 0; i < n && i < 8; ++i) info[i] = vals[i];
   return YYG_OK;
 }
