@@ -511,11 +511,43 @@ void fold_shape(const yyg_grid *g, int *var_ana, int *var_syn, int *nsplit) {
 // Whether the dense FP64 solve of this plan is to run folded: a column in every
 // class (L >= 2), rows within a launch's reach, and work enough to pay for two
 // more launches (tuned plans: 1.0e6 products 22.7 us folded against 19.0,
-// 1.2e7 26.4 against 30.0).
+// 1.2e7 26.4 against 30.0) ...
 constexpr double kFoldMinMacs = 4e6;
-bool fold_wanted(const yyg_grid *g) {
+bool fold_large(const yyg_grid *g) {
   const long M = (long)g->n_patch * g->n_r;
   return g->L >= 2 && M <= 65535 && (double)M * g->nang * g->Q * (1 + g->n_patch) >= kFoldMinMacs;
+}
+
+// ... and for the two passes over the density and the potential, which at low
+// degrees cost more than the products that they save.  Solves, us, unfolded
+// and folded: from degree 8 on the fold is always the faster (900 shells, 92 x
+// 272 x 2: 611 and 572); at degrees 5 to 7 while the density, its fold and the
+// potential fit the last-level cache together (degree 6, 200 shells of 47 x
+// 137 x 2, 21 MB each: 61 and 58; 92 x 272 x 2, 80 MB: 130 and 122 to 129;
+// 900 shells of 47 x 137 x 2, 93 MB: 145 and 177; of 92 x 272 x 2: 418 and
+// 531; degree 5 at 80 MB: 109 and 129); below, only where few rows of many
+// cells leave the unfolded analysis' CUs idle (degree 3, 50 shells of 92 x 272
+// x 2: 65 and 61; 100 shells: 71 and 77; 200 of 24 x 70 x 2: 25 and 31).
+bool fold_wanted(const yyg_grid *g) {
+  if (!fold_large(g)) return false;
+  const long M = (long)g->n_patch * g->n_r;
+  if (g->L >= 5) return g->L >= 8 || 8.0 * M * g->nang <= (g->L == 5 ? 64e6 : 85e6);
+  return g->n_patch == 2 && M <= 50 * g->L && g->nang > 12000;
+}
+
+// Tiles and split of a new plan of that size that solves unfolded: 32 x 32
+// tiles, 64 x 64 (variant 11) where the columns and the rows fill them, and
+// splits that grow with the root of the contraction and shrink with the rows,
+// since the scan reads every split's moments.  Degree 3, us, splits 4 / 8 / 16
+// / 32: 200 shells of 24 x 70 x 2 27 / 25 / 28 / 38, of 47 x 137 x 2 76 / 53 / 44
+// / 48, of 92 x 272 x 2 243 / 144 / 97 / 85; 900 shells: 57 / 60 / 74 / 106, 113 /
+// 100 / 106 / 134 and 467 / 340 / 302 / 337.
+void low_degree_shape(const yyg_grid *g, int *var_ana, int *var_syn, int *nsplit) {
+  const long M = (long)g->n_patch * g->n_r;
+  *var_ana = g->L >= 5 ? 11 : 10;
+  *var_syn = 8.0 * M * g->nang > 64e6 ? 11 : 10;
+  const double split = std::sqrt((double)g->nang) / 4.75 * std::sqrt(std::min(1.0, 600.0 / M));
+  *nsplit = std::max(1, std::min(32, (int)std::lround(split)));
 }
 
 // The fold's tables, built on a stream of their own (no other stream has to
@@ -1931,6 +1963,10 @@ int yyg_grid_create(const yyg_grid_desc *d, int device, yyg_grid **out) {
     yyg::gemm_f64_variant_tile(g->var_ana, &bm, &bn);
     g->nsplit = yyg::choose_split(((M + bm - 1) / bm) * ((Q + bn - 1) / bn), g->nang);
     g->part_cap = g->nsplit;
+    if (fold_large(g) && !fold_wanted(g)) {
+      low_degree_shape(g, &g->var_ana, &g->var_syn, &g->nsplit);
+      g->part_cap = g->nsplit;
+    }
     if (fold_wanted(g)) fold_shape(g, &g->fold.var_ana, &g->fold.var_syn, &g->fold.nsplit);
   }
 

@@ -55,16 +55,30 @@ def test_every_tile_and_split_unfolded(n_r, lmax):
     (13, 12, 32, 11, 1),     # 4.3e6
     (12, 12, 32, 11, 0),     # 4.0e6 less 0.5%
     (400, 24, 70, 1, 0),     # an odd sine class would be empty
+    # low degrees, where the fold's passes cost more than its products save
+    (200, 24, 70, 4, 0),
+    (200, 24, 70, 5, 1),
+    (50, 92, 272, 4, 1),     # few rows of many cells
+    (101, 92, 272, 4, 0),
+    (700, 47, 137, 5, 0),    # 72 MB
+    (700, 47, 137, 6, 1),
+    (850, 47, 137, 7, 0),    # 88 MB
+    (850, 47, 137, 8, 1),
 ])
 def test_which_plans_fold(n_r, n_theta, n_phi, lmax, folded):
     yyg = _yyg()
     g = yyg.Grid(_grid(n_r, n_theta, n_phi, lmax), 0)
     rho = np.random.default_rng(2).uniform(0.1, 1.0, g.shape)
-    dense = _solve(g, rho)
+    dense, mom = _solve(g, rho), g.moments()
     assert g.plan_info()["folded"] == folded
-    for p in ("fp32", "bf16x3", "fp16x2"):
-        g.prepare(p)
-        assert g.plan_info(p)["folded"] == 0
+    # tuned: the moments of the last solve stay
+    g.autotune("fp64")
+    assert np.array_equal(g.moments(), mom)
+    tuned = _solve(g, rho)
+    assert g.plan_info()["folded"] == folded
+    g.prepare("fp32")
+    assert g.plan_info("fp32")["folded"] == 0
     g.set_method("separable")
     sep = _solve(g, rho)
-    assert np.abs(dense - sep).max() <= TOL * np.abs(sep).max()
+    for phi in (dense, tuned):
+        assert np.abs(phi - sep).max() <= TOL * np.abs(sep).max()
