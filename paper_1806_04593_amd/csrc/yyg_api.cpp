@@ -1034,20 +1034,39 @@ void sep_theta_tables(yyg_grid *g, const std::vector<double> &T, const std::vect
   }
 }
 
-// Default kernels of the phi phases on a folded grid.
+// Default kernels of the phi phases on a folded grid: those of
+// yyg_phi_quad.hip, or the 32 x 32 tiles (S.var's start) where a row tile's
+// cells, which a wave of the sweep takes in turn, are many and the waves few.
 void sep_default_phi(yyg_grid *g) {
   auto &S = g->sep;
   const int base = 2 * yyg::gemm_f64_variant_count() + yyg::phi_direct_variant_count();
   const int ana = yyg::phi_quad_default(true, S.quad_ana, g->cus);
-  // without partners a short analysis gains nothing from the parity split:
-  // 131 shells of 61 x 187 cells, lmax 23: 11.2 us in the 32 x 32 tiles, 11.6
-  // in the sweep; nor does one of fewer row tiles than four a CU, whose few
-  // waves each run every stage in turn (a solve, us: 100 shells of 90 x 180
-  // cells, one patch, lmax 12 29.5 and 30.6; 200 of 32 x 92, lmax 16 30.8 and
-  // 31.5; 400 of 47 x 137, 2350 row tiles, the sweep by 2)
-  const long tiles = (long)g->n_t * (((long)g->n_patch * g->n_r + 15) / 16);
-  if (ana == 0 || (S.quad_ana.T2 > 0 && tiles >= 4L * g->cus)) S.var[0] = base + ana;
-  S.var[4] = base + yyg::phi_quad_default(false, S.quad_syn, g->cus);
+  const int syn = yyg::phi_quad_default(false, S.quad_syn, g->cus);
+  const long tiles = (long)g->n_t * (((long)g->n_patch * g->n_r + 15) / 16), cus = g->cus;
+  // Analysis.  Without partners a short one gains nothing from the parity
+  // split: 131 shells of 61 x 187 cells, lmax 23: 11.2 us in the tiles, 11.6 in
+  // the sweep; nor does one of fewer row tiles than four a CU (a solve, us:
+  // 100 shells of 90 x 180 cells, one patch, lmax 12 29.5 and 30.6; 200 of
+  // 32 x 92, lmax 16 30.8 and 31.5; 400 of 47 x 137, 2350 row tiles, the sweep
+  // by 2); nor one of low degree on rows too long for the form with the basis
+  // in registers until twelve a CU (400 shells of 90 x 1000, lmax 10 228 and
+  // 238; 300 of 180 x 1000, 3420 row tiles, 336 and 330; lmax 30 249 and 248).
+  const bool long_ana = S.quad_ana.S > 12 && g->L < 24 && tiles < 12 * cus;
+  if (ana == 0 || (S.quad_ana.T2 > 0 && tiles >= 4 * cus && !long_ana)) S.var[0] = base + ana;
+  // Synthesis, a solve in the tiles and in the sweep, us.  Few row tiles: 14
+  // of 2 x 2000 cells, lmax 8 40 and 64; 160 of 40 x 800, lmax 10 33 and 41; 400
+  // of 25 x 320, lmax 10 29.2 and 31.1; 640 of 40 x 320 33.6 and 33.8; 500 of
+  // 20 x 840, lmax 20 60 and 57.  Long rows of few columns, which the sweep
+  // keeps open all its life: 2250 row tiles of 90 x 1000 cells, lmax 10 206 and
+  // 238, lmax 30 238 and 248, lmax 40 292 and 283; 960 of 60 x 1000, lmax 10 71
+  // and 73, lmax 20 87 and 78; without partners 5700 of 150 x 450, lmax 10 235
+  // and 252, 2500 of 100 x 500, lmax 20 144 and 142; 3420 of 180 x 1600, lmax 10
+  // 404 and 375.  One column (lmax 0): three of the sweep's four sums are empty
+  // (300 shells of 92 x 272 x 2: 63 and 66).
+  const int cells = S.quad_syn.S;
+  const bool few = cells >= 3 && 4 * tiles < 7 * cus;
+  const bool long_syn = cells > 12 && cells <= 20 && g->L < (S.quad_syn.T2 > 0 && tiles >= 8 * cus ? 32 : 16);
+  if (g->L > 0 && (syn == 0 || (!few && !long_syn))) S.var[4] = base + syn;
 }
 
 int sep_build(yyg_grid *g) {
