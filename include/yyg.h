@@ -443,7 +443,8 @@ int yyg_sep_phase(yyg_grid *g, int phase, double *phi, void *stream);
  * with the reduced-precision operand splits): all fields' analysis tiles,
  * then all radial scans, then all synthesis tiles (n_r <= 1024).  Each
  * launch's blocks walk a device work list.  Yin-Yang and polar plans may
- * be mixed.
+ * be mixed.  A field's potential equals its plan's own solve up to FP64
+ * summation order (the two choose their kernels separately).
  * The launches, together with the copy of the
  * per-field arguments, are recorded once into a HIP graph and replayed.
  * `grids` are borrowed and must outlive the batch; all on one device; for

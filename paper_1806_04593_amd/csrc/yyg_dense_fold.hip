@@ -10,7 +10,7 @@
 // products.  Class c = 2 (odd about the equator) + (odd about the meridian).
 // The density is folded once before the analysis and the four classes'
 // potentials are unfolded after the synthesis, each one pass over memory:
-// 82 MB there and back at 2 degrees, 400 shells, some 20 us each.  The four
+// 82 MB there and back at 2 degrees, 400 shells, 14 us each.  The four
 // contractions of a side run in one launch (gemm_nt_f64_quad).
 //
 // Measured, a whole solve unfolded against folded (degree 25 at 2 degrees, 40
@@ -18,7 +18,8 @@
 // 48; 1 degree and 550 shells 5800 and 1600; 5 degrees, 50 shells, degree 8
 // 75 and 27.  Folding the density in the contraction's own loads instead of
 // a pass would fetch every cell once per class and column tile (four to
-// twelve times) for the 20 us.
+// twelve times) for the 14 us.  Low degrees save fewer products than the passes
+// cost; which plans fold stands where they are made.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -42,7 +42,6 @@ __device__ __forceinline__ int quad_xcd(int b, int total) {
 // Buffer descriptor of `bytes` (at most 2^31) from a uniform address: 32-bit
 // lane offsets, and an access at or past the end reads zero or is dropped,
 // so a lane without a place to store carries kNoPlace as its offset.
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kNoPlace = 0x80000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const double *p, long bytes) {
@@ -609,9 +608,10 @@ __global__ __launch_bounds__(64 * rows_max_waves<NQ>()) void phi_syn_rows(PhiQua
 // multiply the previous row tile (double-buffered, one barrier per
 // iteration).  The basis is then read once per block and not once per four
 // row tiles, and a stage costs no barrier.  At half a degree (1000 shells,
-// lmax 64: 1.95 GB, 17 GFLOP) 0.45 ms, 4.3 TB/s, against 0.66 ms for the best
-// form folded once (25 GFLOP) and 0.51 for the sweep; the products alone
-// would take 0.23 ms.
+// lmax 64: 1.95 GB, 17 GFLOP) 0.47 ms in a solve, 4.2 TB/s, against 0.67 ms for
+// the best form folded once (25 GFLOP; the sweep, launched alone, 0.51 against
+// 0.45); the products alone would take 0.23 ms.  Less where a block has few
+// iterations: 550 shells at 1 degree, lmax 40 (286 MB) 106 us, 2.7 TB/s.
 // Four tj waves share a row tile, rtn row tiles run side by side.  LDS holds
 // the even cosines' and even sines' inputs of every point (row stride ldp)
 // and the odd ones' of the paired stages (stride ldq; past them the two
@@ -1012,11 +1012,16 @@ int phi_quad_steps(int L) {
 int phi_quad_variant_count() { return (int)(sizeof(kQuad) / sizeof(kQuad[0])); }
 
 // The registers' form pays for its basis and its first loads once per block:
-// from four iterations a block it is the faster (analysis / synthesis, us:
-// 12 iterations, 550 shells at 1 degree, lmax 40: 77 / 59 against 85 / 81
-// for the sweep; 89, 1000 shells at 0.5 degree, lmax 64: 452 / 442 against
-// 509 / 674), below it the sweep (2-3, 400 shells at 2 degrees, lmax 25:
-// 16.0 / 16.1 against 14.5 / 14.1).
+// the default from four iterations a block on.  Whole solves, us, with this
+// form and with the sweep.  Analysis: 4.6 iterations (400 shells at 2 degrees,
+// lmax 25) 58 and 59, polar 53 and 56; 9 (800 shells, lmax 25) 93 and 98, lmax
+// 40 141 and 155; 6.8 (300 at 1 degree, lmax 30) 101 and 113; below four the two
+// lie within 5% either way (200 at 2 degrees, lmax 25 45.1 and 45.5).
+// Synthesis: 800 shells at 2 degrees 93 and 93; 300 at 1 degree, lmax 30 101 and
+// 105; 400 at 0.75, lmax 40 240 and 271; 1000 at half a degree, lmax 64 441 and
+// 674 alone; but not at degrees 48 to 63, whose seven and eight steps run as
+// nine: 300 at 1 degree, lmax 50 171 and 167; polar 1.5 degrees, lmax 60 129
+// and 94.
 int phi_quad_default(bool analysis, const PhiQuadArgs &a, int cus) {
   const long tiles = (long)a.nt * ((a.Mr + 15) / 16);
   long side = 0;

@@ -16,7 +16,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <climits>
 #include <cstdio>
 
 #include "yyg_internal.h"
@@ -33,9 +32,11 @@ typedef double dbl2t __attribute__((ext_vector_type(2), aligned(16)));
 // wave walks row tiles of 16 rows and loads the next four steps (16 mirror
 // pairs) while it multiplies the last four; the products are basis x data,
 // so that a store covers 16 consecutive rows.  Every X2 value is read once
-// (the tiles read it once per 32 degrees).  Bound by that stream: 1000 shells
-// at half a degree, lmax 64 (444 MB) 147 us in 32 x 32 tiles, 130 in the best
-// tile, 106 here (4.2 TB/s); 800 shells, 180 colatitudes, lmax 80: 95 -> 46.
+// (the tiles read it once per 32 degrees).  Bound by that stream (within whole
+// solves, median of 20 traced): 1000 shells at half a degree, lmax 64 (443 MB)
+// 136 us in 32 x 32 tiles, 105 here (4.2 TB/s); 800 shells, 180 colatitudes,
+// lmax 80 (227 MB) 89 in 32 x 32 tiles, 81 in the best, 59 here (3.8);
+// launched alone, its operands in the last-level cache, 46.
 template <int T>
 __device__ __forceinline__ void theta_ana_sweep(const ThetaArgs &a, const double *Bs, int mc, int m, int ng, int t_beg,
                                                 int t_end, int nw) {
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(64 * NW) void theta_ana_stream(ThetaArgs a, int chu
 
 // The same over the columns of several plans: items (plan, column, chunk,
 // chunks), one a block.  24 plans of 100 to 600 shells at 2 to 4 degrees, lmax
-// 10 to 30: analysis 65 us in tiles, 59 here; synthesis 78, 58; rotation 63,
+// 10 to 30: analysis 65 us in tiles, 60 here; synthesis 78, 57; rotation 63,
 // 40.
 template <int TM, int NW>
 __global__ __launch_bounds__(64 * NW) void theta_ana_group(const ThetaArgs *__restrict__ args,
@@ -138,8 +139,8 @@ __global__ __launch_bounds__(64 * NW) void theta_ana_group(const ThetaArgs *__re
 // Ut[mc][l][row].  A block holds the column's folded basis in LDS; each wave
 // walks row tiles, a tile's coefficients (KQ steps of four degrees per
 // parity) in registers and the next tile's on their way, and stores 16 rows
-// of each colatitude and of its mirror.  Same sizes as above: 171 us in
-// 64 x 32 tiles, 138 in the best tile, 105 here; 70 -> 49.
+// of each colatitude and of its mirror.  Same sizes as above: 152 us in
+// 64 x 32 tiles, 139 in the best tile, 98 here (4.5 TB/s); 88, 84 and 69 (3.3).
 template <int KQ, int NW>
 __device__ __forceinline__ void theta_syn_block(const ThetaArgs &a, double *Bs, int mc, int chunk, int chunks) {
   const int m = (mc + 1) >> 1;
@@ -241,8 +242,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t theta_buffer(const double *p, 
 // member 4 q + g): they are the B operand for the other patch and, value
 // 4 t + r being element r of output tile t, the accumulators' start for
 // their own.  So the moments are read once and written once (the tiles read
-// them twice): 1000 shells, lmax 64 (135 MB) 67 us in tiles, 59 with a wave
-// per class and patch, 35 here (3.9 TB/s).  At most KQ steps of four members, NT tiles of 16.
+// them twice): 1000 shells, lmax 64 (135 MB) 67 us in tiles, 45 here (3.0 TB/s;
+// launched alone 35, and 59 with a wave per class and patch).  At most KQ steps of four members, NT tiles of 16.
 template <int NT, int KQ>
 __device__ __forceinline__ void rotation_block(const ThetaArgs &a, double *Ds, int l, int unit, int run, int runs) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -426,7 +427,6 @@ bool theta_stream_fits(int phase, int L, int h) {
 
 hipError_t launch_theta_stream(int phase, int variant, const ThetaArgs &a, int cus, hipStream_t s) {
   if (a.Mr <= 0 || a.nt <= 0) return hipSuccess;
-  if ((long)(2 * a.L + 1) * 4096 > INT_MAX) return hipErrorInvalidValue;
   switch (phase) {
     case 1: return variant ? launch_theta_ana_w<4>(a, cus, s) : launch_theta_ana_w<8>(a, cus, s);
     case 2: return launch_rotation(a, variant ? 2 : 1, cus, s);
