@@ -146,8 +146,9 @@ int yyg_prepare(yyg_grid *g, int precision);
  *  YYG_METHOD_DENSE      the two angular contractions as dense MFMA
  *                        contractions over all angular cells (Eqs. 26-27 and
  *                        5, 28-29 written as matrix products): 2Q + 4Q flops
- *                        per cell.  FP64 from degree 2 on and about 4e6
- *                        products contracts over a quarter of the patch, by
+ *                        per cell.  FP64 from about 4e6 products and degree 8
+ *                        on (lower degrees at the sizes where it pays)
+ *                        contracts over a quarter of the patch, by
  *                        the two mirror symmetries: a quarter of that, for
  *                        one density-sized buffer and a quarter of the bases
  *                        more memory (unfolded where that is not to be had).
