@@ -1336,9 +1336,11 @@ int sep_build(yyg_grid *g) {
                            (long)yyg::theta_syn_doubles(L, (nt + 1) / 2), (long)yyg::rotation_doubles(L), L, g->n_r, (int)M, nt, (nt + 1) / 2};
   // the theta synthesis' waves each run a column's colatitudes in turn: where
   // they are few and the colatitudes many, 32 x 32 tiles (a solve, us: 25
-  // columns of 7 row tiles, 90 colatitudes 29.6 and 30.6; 41 of 13, 60 29.2
-  // and 30.0; 33 of 25, 32 colatitudes the same)
-  const bool few = (long)nmc * ((M + 15) / 16) < 3L * g->cus && nt > 48;
+  // columns of 7 row tiles, 90 colatitudes 29.6 and 30.6; 33 of 7, 47
+  // colatitudes 29.8 and 30.9; 81 of 7 43.2 and 43.9; 51 of 13 35.7 and 36.5; 21 of
+  // 13, 32 colatitudes 25.5 and 26.4; 51 of 25, 47 colatitudes 44.6 and 44.4;
+  // 17 of 4, 20 colatitudes 23.9 and 24.2)
+  const bool few = (long)nmc * ((M + 15) / 16) < 3L * g->cus && nt > 24;
   for (int r = 1; r <= 3; ++r)
     if (S.stream[r]) S.var[r] = r == 3 && few ? 10 : yyg::gemm_f64_variant_count() + 4;
   S.ready = true;

@@ -1,4 +1,4 @@
-"""The phi kernels a separable plan starts from: the 32 x 32 tiles where the
+"""The kernels a separable plan starts from: the 32 x 32 tiles where the
 sweeps' waves are few or hold long rows of few columns, against the sweeps."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ from paper_1806_04593_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 TOL = 1e-12    # the FP64 gate of the potential
-ANA_SWEEP, SYN_SWEEP = 38, 37
+ANA_SWEEP, SYN_SWEEP, THETA_STREAM = 38, 37, 18
 
 
 def _polar(n_t, n_p, n_r, lmax):
@@ -44,12 +44,34 @@ def test_default_form(d, ana, syn):
     names = g.sep_kernel(0), g.sep_kernel(4)
     print(names, flush=True)
     assert (ana is None or ana in names[0]) and syn in names[1], names
+    _against(torch, g, (0, ANA_SWEEP), (4, SYN_SWEEP))
+
+
+@pytest.mark.parametrize("d, tile", [
+    (_yy(47, 137, 50, 25), True),      # 51 columns of 7 row tiles
+    (_yy(25, 71, 100, 28), True),      # 57 of 13, 25 colatitudes
+    (_yy(24, 68, 100, 28), False),
+    (_yy(47, 137, 200, 15), False),    # 31 of 25
+], ids=["few", "25", "24", "more"])
+def test_default_theta_synthesis(d, tile):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1806_04593_amd import yyg
+    g = yyg.Grid(d, 0)
+    g.set_method("separable")
+    assert ("stream" in g.sep_kernel(3)) != tile, g.sep_kernel(3)
+    _against(torch, g, (3, THETA_STREAM))
+
+
+def _against(torch, g, *config):
+    """The plan as created against its kernels named by phase and variant."""
     rho = torch.rand(g.shape, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3)) + 0.1
     got, ref = torch.full_like(rho, float("nan")), torch.full_like(rho, float("nan"))
     g.upload_rho(rho)
     g.solve(got)
-    g.sep_config(0, ANA_SWEEP)
-    g.sep_config(4, SYN_SWEEP)
+    for phase, variant in config:
+        g.sep_config(phase, variant)
+        assert "quad" in g.sep_kernel(phase) or "stream" in g.sep_kernel(phase)
     g.solve(ref)
-    assert "quad" in g.sep_kernel(0) and "quad" in g.sep_kernel(4)
     assert float(((got - ref) / ref).abs().max()) <= TOL
