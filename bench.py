@@ -16,7 +16,6 @@ separable FP64 form).
 import argparse
 import hashlib
 import json
-import math
 import os
 import re
 import sys
@@ -264,19 +263,13 @@ def phi_folded(kname):
                 or (kname.startswith("yyg::gemm_nt_f64_batched<") and int(args[-1]) & (128 | 256 | 4096)))
 
 
-def phi_share(kname, desc):
+def phi_share(kname, desc, points):
     """The share of the unfolded multiply-adds a phi-transform kernel needs:
-    half for rows folded about the central meridian; folded about the
-    meridians 90 degrees off it too, the folded points over the cells (where
-    the spacing divides 180 degrees; else half)."""
-    if not re.search(r"::phi_(ana|syn)_(rows|quad)<", kname):
-        return 0.5 if phi_folded(kname) else 1.0
-    n_p = desc["n_phi"]
-    span = 2.0 * math.pi if desc.get("kind") == "polar" else 1.5 * math.pi + 2.0 * desc["delta_phi"]
-    c = n_p - 1 - math.pi * n_p / span
-    h, cc = (n_p + 1) // 2, round(c)
-    paired = abs(c - cc) < 1e-6 and 1 <= cc < h
-    return (h - (cc + 1) // 2 if paired else h) / n_p
+    half for rows folded about the central meridian; the plan's folded points
+    over the cells for the kernels folded about two."""
+    if re.search(r"::phi_(ana|syn)_(rows|quad)<", kname):
+        return points / desc["n_phi"]
+    return 0.5 if phi_folded(kname) else 1.0
 
 
 def phi_roofline(head, desc, M, nang):
@@ -294,7 +287,7 @@ def phi_roofline(head, desc, M, nang):
     # per-phase events inside solves add a launch gap to each)
     ms_k = head["phase_alone_ms"][name]
     kname = head["kernel_names"][name]
-    flops_k *= phi_share(kname, desc)
+    flops_k *= phi_share(kname, desc, head.get("phi_points"))
     tf = flops_k / (ms_k * 1e-3) / 1e12
     gbs = bytes_k / (ms_k * 1e-3) / 1e9
     fm, fh = tf / PEAK["fp64"], gbs / 8000.0
@@ -372,14 +365,14 @@ def bench_single(a):
         phi_flops = 2.0 * M * nang * L2           # each phi transform (unfolded count)
         # algorithmic TFLOP/s of each phi transform in the solve
         names = {p: g.sep_kernel(q) for p, q in (("phi_analysis", 0), ("phi_synthesis", 4))}
-        alg = {p: phi_flops * phi_share(n, desc) for p, n in names.items()}
+        alg = {p: phi_flops * phi_share(n, desc, g.phi_points()) for p, n in names.items()}
         results["fp64_separable"] = {
             "cells_per_s": cells / (ms * 1e-3), "ms_per_step": ms, "max_rel_err_vs_oracle": err,
             "kernels_ms": {"phi_analysis": avg[4], "theta_analysis_rotation": avg[5], "radial_scan": avg[1],
                            "theta_synthesis": avg[6], "phi_synthesis": avg[7]},
             "phi_synthesis_tflops": alg["phi_synthesis"] / (avg[7] * 1e-3) / 1e12,
             "phi_analysis_tflops": alg["phi_analysis"] / (avg[4] * 1e-3) / 1e12,
-            "phase_alone_ms": alone, "variants": g.sep_info(), "tune_s": round(tune_s, 2),
+            "phase_alone_ms": alone, "variants": g.sep_info(), "phi_points": g.phi_points(), "tune_s": round(tune_s, 2),
             "kernel_names": {n: g.sep_kernel(p) for p, n in enumerate(
                 ("phi_analysis", "theta_analysis", "rotation", "theta_synthesis", "phi_synthesis"))},
         }

@@ -184,7 +184,9 @@ int yyg_set_method(yyg_grid *g, int method);
  * both patches in their own local coordinates).  rho_is_device != 0: `rho` is a device
  * array that the plan borrows (no copy) and that must stay valid until the
  * next yyg_solve on `stream` completes.  rho_is_device == 0: host array,
- * copied into plan-owned device memory on `stream`. */
+ * copied into plan-owned device memory on `stream`.  The first density of a
+ * plan in the dense form may build the folded solve's tables
+ * (YYG_METHOD_DENSE). */
 int yyg_upload_rho(yyg_grid *g, const double *rho, int rho_is_device, void *stream);
 
 /* Solve Phi for the last uploaded density: the per-patch weighted moments
@@ -389,7 +391,10 @@ int yyg_sep_config(yyg_grid *g, int phase, int variant);
 int yyg_sep_variant_count(int phase);
 
 /* variants[0..4] = the separable form's tile variant per phase (-1 for
- * phase 2 on a polar grid, and for every phase before the form is built). */
+ * phase 2 on a polar grid, and for every phase before the form is built),
+ * variants[5] = the points a row of cells folds to in the phi kernels folded
+ * about two meridians (0 on a grid without the fold, and before); first n
+ * entries. */
 int yyg_sep_info(const yyg_grid *g, int *variants, int n);
 
 /* The kernel that runs separable phase `phase` (0-4, as for yyg_sep_config)

@@ -2858,6 +2858,7 @@ int yyg_sep_info(const yyg_grid *g, int *variants, int n) {
   if (!g || !variants || n < 1) return YYG_ERR_INVALID_ARG;
   for (int i = 0; i < n && i < 5; ++i)
     variants[i] = (!g->sep.ready || (i == 2 && g->n_patch != 2)) ? -1 : g->sep.var[i];
+  if (n > 5) variants[5] = g->sep.ready && g->sep.fold ? g->sep.quad_syn.K : 0;
   return YYG_OK;
 }
 

@@ -288,6 +288,12 @@ class Grid:
         _check(lib().yyg_sep_info(self._h, v, 5), "yyg_sep_info")
         return list(v)
 
+    def phi_points(self):
+        """yyg_sep_info's sixth entry: points per row of the twice-folded phi kernels."""
+        v = (ctypes.c_int * 6)()
+        _check(lib().yyg_sep_info(self._h, v, 6), "yyg_sep_info")
+        return v[5]
+
     def sep_kernel(self, phase):
         buf = ctypes.create_string_buffer(256)
         _check(lib().yyg_sep_kernel(self._h, int(phase), buf, 256), "yyg_sep_kernel")

@@ -75,3 +75,23 @@ def _against(torch, g, *config):
         assert "quad" in g.sep_kernel(phase) or "stream" in g.sep_kernel(phase)
     g.solve(ref)
     assert float(((got - ref) / ref).abs().max()) <= TOL
+
+
+@pytest.mark.parametrize("d, points", [
+    (_polar(20, 180, 3, 4), 45),       # a quarter of the row
+    (_polar(20, 181, 3, 4), 91),       # odd rows: no partners
+    (W.make_desc("half", np.linspace(0.0, 1.0, 3), 2.0, 4, 0.9, 0), 46),   # 137 cells of 2 degrees
+    (_yy(30, 91, 3, 4), 46),           # no partners: half the row
+])
+def test_reported_fold(d, points):
+    """The share of a row that the twice-folded kernels contract over, for
+    whoever counts their work: cells k and cc - k of the front half pair up."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1806_04593_amd import yyg
+    g = yyg.Grid(d, 0)
+    assert g.phi_points() == 0
+    g.set_method("separable")
+    assert g.phi_points() == points
+    assert len(g.sep_info()) == 5
